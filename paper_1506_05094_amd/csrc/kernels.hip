@@ -325,115 +325,122 @@ __device__ __forceinline__ void pair_acc(const float4 pi, const Wide &wi, const 
     }
     return;
   }
-  if (METHOD == 3) {
-    // shifted-force Lennard-Jones inside r_c,ab plus shifted-force Coulomb inside r_cc
-    // (paper section 9): q_a q_b (1/r - 1/r_cc + (r - r_cc)/r_cc^2), force
-    // q_a q_b (1/r^2 - 1/r_cc^2); each term has its own float32 in/out decision
-    const CoulRow &cr = sp.crow[pidx];
-    const bool in_lj = r2s < pr.rc2, in_c = r2s < cr.rcc2;
-    if (in_lj || in_c) {
-      dx = (float)(((double)pj.x - wi.x) - (double)mx * c.Ld[0]);
-      dy = (float)(((double)pj.y - wi.y) - (double)my * c.Ld[1]);
-      dz = (float)(((double)pj.z - wi.z) - (double)mz * c.Ld[2]);
-      const float r2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
-      const float inv_r2 = __builtin_amdgcn_rcpf(r2);
-      const float inv_r = __builtin_amdgcn_rsqf(r2);
-      const float r = r2 * inv_r;
-      float fr = 0.f, e = 0.f;
-      if (in_lj) {
-        const float s2 = pr.sig2 * inv_r2;
-        const float s6 = s2 * s2 * s2;
-        const float s12 = s6 * s6;
-        fr = __builtin_fmaf(-pr.fc, inv_r, pr.eps24 * __builtin_fmaf(2.0f, s12, -s6) * inv_r2);
-        e = __builtin_fmaf(r - pr.rc, pr.fc, __builtin_fmaf(pr.eps4, s12 - s6, -pr.ushift));
-      }
-      if (in_c) {
-        fr = __builtin_fmaf(cr.qq * inv_r, inv_r2 - cr.inv_rcc2, fr);
-        e = __builtin_fmaf(cr.qq, __builtin_fmaf(r, cr.inv_rcc2, inv_r) - cr.two_inv_rcc, e);
-      }
-      fx = __builtin_fmaf(-fr, dx, fx);
-      fy = __builtin_fmaf(-fr, dy, fy);
-      fz = __builtin_fmaf(-fr, dz, fz);
-      u += e;
-      w = __builtin_fmaf(fr, r2, w);
-    }
-    return;
+}
+
+// One pair contribution of 12-6 Lennard-Jones (paper section 2 cutoff methods;
+// METHOD 0-2) or of shifted-force Lennard-Jones plus shifted-force Coulomb (METHOD 3,
+// paper section 9: q_a q_b (1/r - 1/r_cc + (r - r_cc)/r_cc^2), force
+// q_a q_b (1/r^2 - 1/r_cc^2), each term with its own float32 in/out decision).
+// Straight-line code: a pair out of range (or ok = false, an idle slot) contributes
+// zeros by selects instead of a branch, so the pairs of a batch are independent
+// instruction streams that the compiler interleaves.  IMG = false: the caller knows
+// that no pair in range crosses the periodic boundary; then every image integer is 0,
+// the float32 differences are the correctly rounded ones and both the decision and the
+// value use them (the same bits as the general form).  ONE: a single particle type,
+// whose constants are uniform over the wave (scalar registers) instead of LDS rows.
+template <int METHOD, bool IMG, bool ONE>
+__device__ __forceinline__ void lj_pair(const float4 pi, const Wide &wi, const float4 pj, bool ok, int row0,
+                                        const SharedPairs &sp, const SysConst &c, float &fx, float &fy, float &fz,
+                                        float &u, float &w) {
+  float dx = pj.x - pi.x, dy = pj.y - pi.y, dz = pj.z - pi.z;
+  float mx = 0.f, my = 0.f, mz = 0.f;
+  if (IMG) {
+    mx = __builtin_rintf(dx * c.invL[0]);
+    my = __builtin_rintf(dy * c.invL[1]);
+    mz = __builtin_rintf(dz * c.invL[2]);
+    dx = __builtin_fmaf(-mx, c.L[0], dx);
+    dy = __builtin_fmaf(-my, c.L[1], dy);
+    dz = __builtin_fmaf(-mz, c.L[2], dz);
   }
-  if (r2s < pr.rc2) {
+  const float r2s = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
+  const int pidx = ONE ? 0 : row0 + ptype(pj);
+  const float rc2 = ONE ? c.pt.rc2[0] : sp.row[pidx].rc2, sig2 = ONE ? c.pt.sig2[0] : sp.row[pidx].sig2;
+  const float eps24 = ONE ? c.pt.eps24[0] : sp.row[pidx].eps24, eps4 = ONE ? c.pt.eps4[0] : sp.row[pidx].eps4;
+  const float ushift = ONE ? c.pt.ushift[0] : sp.row[pidx].ushift;
+  const bool in_lj = ok & (r2s < rc2);
+  float r2 = r2s;
+  if (IMG) {
     dx = (float)(((double)pj.x - wi.x) - (double)mx * c.Ld[0]);
     dy = (float)(((double)pj.y - wi.y) - (double)my * c.Ld[1]);
     dz = (float)(((double)pj.z - wi.z) - (double)mz * c.Ld[2]);
-    const float r2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
-    const float inv_r2 = __builtin_amdgcn_rcpf(r2);
-    const float s2 = pr.sig2 * inv_r2;
-    const float s6 = s2 * s2 * s2;
-    const float s12 = s6 * s6;
-    float fr = pr.eps24 * __builtin_fmaf(2.0f, s12, -s6) * inv_r2;
-    float e = __builtin_fmaf(pr.eps4, s12 - s6, -pr.ushift);
-    if (METHOD == 2) {  // shifted force: F(r) - F(rc); U(r) - U(rc) + (r - rc) F(rc)
-      const float inv_r = __builtin_amdgcn_rsqf(r2);
-      const float r = r2 * inv_r;
-      fr = __builtin_fmaf(-pr.fc, inv_r, fr);
-      e = __builtin_fmaf(r - pr.rc, pr.fc, e);
-    }
-    fx = __builtin_fmaf(-fr, dx, fx);
-    fy = __builtin_fmaf(-fr, dy, fy);
-    fz = __builtin_fmaf(-fr, dz, fz);
-    u += e;
-    w = __builtin_fmaf(fr, r2, w);
+    r2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
   }
+  const float inv_r2 = __builtin_amdgcn_rcpf(r2);
+  const float s2 = sig2 * inv_r2;
+  const float s6 = s2 * s2 * s2;
+  const float s12 = s6 * s6;
+  float fr = eps24 * __builtin_fmaf(2.0f, s12, -s6) * inv_r2;
+  float e = __builtin_fmaf(eps4, s12 - s6, -ushift);
+  if (METHOD >= 2) {  // shifted force: F(r) - F(rc); U(r) - U(rc) + (r - rc) F(rc)
+    const float fc = ONE ? c.pt.fc[0] : sp.row[pidx].fc, rc = ONE ? c.pt.rc[0] : sp.row[pidx].rc;
+    const float inv_r = __builtin_amdgcn_rsqf(r2);
+    const float r = r2 * inv_r;
+    fr = __builtin_fmaf(-fc, inv_r, fr);
+    e = __builtin_fmaf(r - rc, fc, e);
+    if (METHOD == 3) {
+      const CoulRow &cr = sp.crow[pidx];
+      const bool in_c = ok & (r2s < cr.rcc2);
+      fr = in_lj ? fr : 0.f;
+      e = in_lj ? e : 0.f;
+      const float frc = __builtin_fmaf(cr.qq * inv_r, inv_r2 - cr.inv_rcc2, fr);
+      const float ec = __builtin_fmaf(cr.qq, __builtin_fmaf(r, cr.inv_rcc2, inv_r) - cr.two_inv_rcc, e);
+      fr = in_c ? frc : fr;
+      e = in_c ? ec : e;
+    }
+  }
+  if (METHOD != 3) {
+    fr = in_lj ? fr : 0.f;
+    e = in_lj ? e : 0.f;
+  }
+  fx = __builtin_fmaf(-fr, dx, fx);
+  fy = __builtin_fmaf(-fr, dy, fy);
+  fz = __builtin_fmaf(-fr, dz, fz);
+  u += e;
+  w = __builtin_fmaf(fr, r2, w);
 }
 
-// Force on particle i from lane t of its TP lanes (entries k = t, t+TP, ...).
-// The lane's entries are taken B at a time: B list indices are loaded together,
-// then the B neighbour positions, so a batch costs two memory round trips instead
-// of two per entry (the paper prefetches one entry ahead, section 5; on MI355X the
-// latency of a dependent load chain dominates, so many loads go in flight).  The
-// first batch is issued before the list length arrives (clamped to the capacity
-// n_max / TP of a lane), so the length and the first indices share a round trip.
-template <int TP, int METHOD, int B, bool PF = false, class IdxPtr>
-__device__ __forceinline__ void force_lane(int i, int t, const float4 pi, const float4 *__restrict__ pos,
-                                           IdxPtr nbl, IdxPtr nnb, const SharedPairs &sp, const SysConst &c,
-                                           float &fx, float &fy, float &fz, float &u, float &w) {
+// Pairs evaluated together: a group is skipped (uniformly) once every lane's list has
+// ended.  1, 2 and 4 measured within 1 % of each other; with whole batches of 8 a wave
+// of lists of 10 entries did 16 pairs of work.
+constexpr int kPairGroup = 2;
+
+// The list of one lane (entries k = t, t + TP, ... of particle i; mine of them, at most
+// wmax in this wave), B entries at a time: the positions of a batch are issued
+// together, then the next batch's indices, which arrive while the batch is evaluated.
+// The entries of one slot of all lanes of a wave are consecutive words of the list, so
+// a slot's address is uniform (row + m * stride) plus the lane.
+template <int TP, int METHOD, int B, bool IMG, bool ONE, class IdxPtr>
+__device__ __forceinline__ void force_loop(int i, const float4 pi, const float4 *__restrict__ pos, IdxPtr row,
+                                           long long stride, int mine, int wmax, int (&j)[B], const SharedPairs &sp,
+                                           const SysConst &c, float &fx, float &fy, float &fz, float &u, float &w) {
+  const int lane = threadIdx.x & 63;
   const int ti = ptype(pi);
+  const int row0 = ti * c.ntypes;
   const Wide wi = widen(pi);
-  const long long stride = (long long)c.nvp * TP;
-  const IdxPtr row = nbl + (long long)i * TP + t;
-  const int cap = c.n_max / TP;  // entries of one lane the list can hold
-  int j[B];
-#pragma unroll
-  for (int b = 0; b < B; ++b) j[b] = __builtin_nontemporal_load(row + (long long)min(b, cap - 1) * stride);
-  const int nn = nnb[i];
-  const int mine = nn > t ? (nn - t + TP - 1) / TP : 0;  // entries of this lane
-  for (int m0 = 0; m0 < mine; m0 += B) {
-    if (!PF && m0 > 0) {
-#pragma unroll
-      for (int b = 0; b < B; ++b) {
-        // every load is issued (clamped to the lane's last entry) so none waits behind a branch
-        const int mm = min(m0 + b, mine - 1);
-        j[b] = __builtin_nontemporal_load(row + (long long)mm * stride);
-      }
-    }
-#pragma unroll
-    for (int b = 0; b < B; ++b)
-      if (m0 + b >= mine) j[b] = -1;
+  for (int m0 = 0; m0 < wmax; m0 += B) {
+    bool ok[B];
     float4 q[B];
 #pragma unroll
-    for (int b = 0; b < B; ++b) q[b] = pos[j[b] >= 0 ? j[b] : i];
-    // PF: the next batch's indices are issued after this batch's positions, so they
-    // arrive while this batch is evaluated (and a wait for the positions does not wait
-    // for them)
-    int jn[PF ? B : 1];
-    if (PF && m0 + B < mine) {
+    for (int b = 0; b < B; ++b) {
+      ok[b] = m0 + b < mine;
+      q[b] = pos[ok[b] ? j[b] : i];
+    }
+    if (m0 + B < wmax) {
 #pragma unroll
-      for (int b = 0; b < B; ++b) jn[b] = __builtin_nontemporal_load(row + (long long)min(m0 + B + b, mine - 1) * stride);
+      for (int b = 0; b < B; ++b) j[b] = __builtin_nontemporal_load(row + (long long)min(m0 + B + b, wmax - 1) * stride + lane);
     }
 #pragma unroll
-    for (int b = 0; b < B; ++b)
-      if (j[b] >= 0) pair_acc<METHOD>(pi, wi, q[b], ti, c.ntypes, sp, c, fx, fy, fz, u, w);
-    if (PF && m0 + B < mine) {
+    for (int g = 0; g < B; g += kPairGroup) {
+      if (m0 + g < wmax) {  // uniform
 #pragma unroll
-      for (int b = 0; b < B; ++b) j[b] = jn[b];
+        for (int b = g; b < g + kPairGroup; ++b) {
+          if constexpr (METHOD <= 3) {
+            lj_pair<METHOD, IMG, ONE>(pi, wi, q[b], ok[b], row0, sp, c, fx, fy, fz, u, w);
+          } else {
+            if (ok[b]) pair_acc<METHOD>(pi, wi, q[b], ti, c.ntypes, sp, c, fx, fy, fz, u, w);
+          }
+        }
+      }
     }
   }
 }
@@ -561,6 +568,70 @@ __device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v)
 
 __device__ __forceinline__ int wave_or(int v) {
   return (int)wave_reduce64((unsigned)v, 0ull, [](unsigned long long a, unsigned long long b) { return a | b; });
+}
+
+// Largest of the lanes' non-negative integers, uniform (a scalar register).
+__device__ __forceinline__ int wave_max_i32(int v) {
+  auto up = [](int a, int b) { return a > b ? a : b; };
+  v = up(v, (int)dpp32<kDppXor1, 0xF>(0u, (unsigned)v));
+  v = up(v, (int)dpp32<kDppXor2, 0xF>(0u, (unsigned)v));
+  v = up(v, (int)dpp32<kDppHalfMirror, 0xF>(0u, (unsigned)v));
+  v = up(v, (int)dpp32<kDppMirror, 0xF>(0u, (unsigned)v));
+  v = up(v, (int)dpp32<kDppBcast15, 0xA>(0u, (unsigned)v));
+  v = up(v, (int)dpp32<kDppBcast31, 0xC>(0u, (unsigned)v));
+  return __builtin_amdgcn_readlane(v, 63);
+}
+
+// Force on particle i from lane t of its TP lanes (entries k = t, t+TP, ...), by whole
+// waves: lanes with active = false (i past the end) idle with i clamped to a valid
+// particle.  The lane's entries are taken B at a time (the paper prefetches one entry
+// ahead, section 5; on MI355X the latency of a dependent load chain dominates, so many
+// loads go in flight).  The first batch is issued before the list length arrives
+// (clamped to the capacity n_max / TP of a lane), so the length and the first indices
+// share a round trip.  A wave whose particles are all farther than the cutoff from
+// every face takes the loop without image arithmetic, and a system of one type the
+// loop with scalar constants (25 and 20 instructions of about 60 per pair).
+template <int TP, int METHOD, int B, class IdxPtr>
+__device__ __forceinline__ void force_lane(int i, int t, bool active, const float4 pi, const float4 *__restrict__ pos,
+                                           IdxPtr nbl, IdxPtr nnb, const SharedPairs &sp, const SysConst &c,
+                                           float &fx, float &fy, float &fz, float &u, float &w) {
+  const long long stride = (long long)c.nvp * TP;
+  // particle of the wave's first lane, a multiple of 64 / TP (also in a wave that idles
+  // with its lanes clamped), so that the wave's words stay inside the list's nvp columns
+  const int lane = threadIdx.x & 63;
+  const int i0 = __builtin_amdgcn_readfirstlane(i - lane / TP) & ~(64 / TP - 1);
+  const IdxPtr row = nbl + (long long)i0 * TP;
+  const int cap = c.n_max / TP;  // entries of one lane the list can hold
+  int j[B];
+#pragma unroll
+  for (int b = 0; b < B; ++b) j[b] = __builtin_nontemporal_load(row + (long long)min(b, cap - 1) * stride + lane);
+  const int nn = active ? nnb[i] : 0;
+  const int mine = nn > t ? (nn - t + TP - 1) / TP : 0;  // entries of this lane
+  int wmax = 0;  // entries of the wave's longest lane
+  if constexpr (TP >= 16) {  // few particles per wave: their lengths by scalar reads
+#pragma unroll
+    for (int k = 0; k < 64; k += TP) wmax = max(wmax, __builtin_amdgcn_readlane(nn, k));
+    wmax = (wmax + TP - 1) / TP;
+  } else {
+    wmax = wave_max_i32(mine);
+  }
+  // from 16 lanes per particle the wave at a face sets the pace of the step: one form
+  const bool near = TP >= 16 || fabsf(pi.x) >= c.inner[0] || fabsf(pi.y) >= c.inner[1] || fabsf(pi.z) >= c.inner[2];
+  if constexpr (METHOD <= 3) {
+    if (c.ntypes == 1 && METHOD != 3) {
+      if (TP >= 16 || __any(near))
+        force_loop<TP, METHOD, B, true, true>(i, pi, pos, row, stride, mine, wmax, j, sp, c, fx, fy, fz, u, w);
+      else
+        force_loop<TP, METHOD, B, false, true>(i, pi, pos, row, stride, mine, wmax, j, sp, c, fx, fy, fz, u, w);
+    } else {
+      if (TP >= 16 || __any(near))
+        force_loop<TP, METHOD, B, true, false>(i, pi, pos, row, stride, mine, wmax, j, sp, c, fx, fy, fz, u, w);
+      else
+        force_loop<TP, METHOD, B, false, false>(i, pi, pos, row, stride, mine, wmax, j, sp, c, fx, fy, fz, u, w);
+    }
+  } else {
+    force_loop<TP, METHOD, B, true, false>(i, pi, pos, row, stride, mine, wmax, j, sp, c, fx, fy, fz, u, w);
+  }
 }
 
 // Inclusive prefix sum over the lanes of a wave, exact for integers: within each row
@@ -827,25 +898,25 @@ __device__ void sort_gather(const SysConst &c, const SysPtrs &p, int cur, int fi
   }
 }
 
-__global__ __launch_bounds__(256) void k_bin(SysConst c, SysPtrs p, int cur) {
+static __global__ __launch_bounds__(256) void k_bin(SysConst c, SysPtrs p, int cur) {
   if (p.ctl->rebuild == 0) return;
   sort_bin(c, p, cur, blockIdx.x * blockDim.x, gridDim.x * blockDim.x);
 }
 
 // One workgroup per tile of cells.
-__global__ __launch_bounds__(256) void k_scan(SysConst c, SysPtrs p) {
+static __global__ __launch_bounds__(256) void k_scan(SysConst c, SysPtrs p) {
   if (p.ctl->rebuild == 0) return;
   __shared__ unsigned s_w[16];
   if (blockIdx.x == 0 && threadIdx.x == 0) begin_build(p.ctl);
   sort_scan_tile(c, p, blockIdx.x, s_w);
 }
 
-__global__ __launch_bounds__(256) void k_scatter(SysConst c, SysPtrs p) {
+static __global__ __launch_bounds__(256) void k_scatter(SysConst c, SysPtrs p) {
   if (p.ctl->rebuild == 0) return;
   sort_scatter(c, p, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x, blockIdx.x == 0);
 }
 
-__global__ __launch_bounds__(256) void k_gather(SysConst c, SysPtrs p, int cur) {
+static __global__ __launch_bounds__(256) void k_gather(SysConst c, SysPtrs p, int cur) {
   if (p.ctl->rebuild == 0) return;
   sort_gather(c, p, cur, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
 }
@@ -955,7 +1026,7 @@ __device__ void sort_small_block(const SysConst &c, const SysPtrs &p, int cur, u
 }
 
 // Spatial sort requested from the host (start of a run, new state or parameters).
-__global__ __launch_bounds__(1024) void k_sort_small(SysConst c, SysPtrs p, int cur) {
+static __global__ __launch_bounds__(1024) void k_sort_small(SysConst c, SysPtrs p, int cur) {
   __shared__ unsigned s_cnt[kSmallCells + 1];
   __shared__ int s_id[kSmallN];
   __shared__ int s_due;
@@ -974,7 +1045,9 @@ __global__ __launch_bounds__(1024) void k_sort_small(SysConst c, SysPtrs p, int 
   sort_small_block<1024>(c, p, cur, s_cnt, s_id);
 }
 
+#ifndef SRMD_TP
 bool small_sort_fits(int n, int ncell) { return n <= kSmallN && ncell <= kSmallCells; }
+#endif
 
 // ---------------------------------------------------------------- list builds
 
@@ -1131,7 +1204,7 @@ __device__ int list_allpairs_one(const SysConst &c, const SysPtrs &p, int i, con
 
 // All-pairs lists for the launch chain, one wave per particle, four per block; the
 // particles keep their order unless a periodic re-sort ran before this build.
-__global__ __launch_bounds__(256) void k_list_allpairs(SysConst c, SysPtrs p, int cur) {
+static __global__ __launch_bounds__(256) void k_list_allpairs(SysConst c, SysPtrs p, int cur) {
   if (p.ctl->rebuild == 0) return;
   __shared__ float s_cs2[kMaxPairs];
   if (threadIdx.x < kMaxPairs) s_cs2[threadIdx.x] = c.pt.cs2[threadIdx.x];
@@ -1152,7 +1225,7 @@ __global__ __launch_bounds__(256) void k_list_allpairs(SysConst c, SysPtrs p, in
 }
 
 // One wave per particle (list_wave_one), four particles per block.
-__global__ __launch_bounds__(256) void k_list_wave(SysConst c, SysPtrs p, int cur) {
+static __global__ __launch_bounds__(256) void k_list_wave(SysConst c, SysPtrs p, int cur) {
   if (p.ctl->rebuild == 0) return;
   __shared__ float s_cs2[kMaxPairs];
   __shared__ unsigned s_cand[4][kWaveCand];
@@ -1189,7 +1262,7 @@ __device__ __forceinline__ int wave_min_int(int v) {
 // LDS, and every slot that all lanes of the wave have passed is written out as one
 // span.  A lane that runs kRing slots ahead of the slowest lane writes its later
 // entries directly.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_list_thread(SysConst c, SysPtrs p, int cur) {
+static __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_list_thread(SysConst c, SysPtrs p, int cur) {
   if (p.ctl->rebuild == 0) return;
   __shared__ float s_cs2[kMaxPairs];
   __shared__ int s_ring[4][kRing][64];
@@ -1303,7 +1376,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 constexpr int kRowCap = 1024;    // particles of a stencil row staged in LDS
 constexpr int kRowCells = 1024;  // cells per x-row the cell starts of LDS hold (nc <= 1024)
 
-__global__ __launch_bounds__(256) void k_list_row(SysConst c, SysPtrs p, int cur) {
+static __global__ __launch_bounds__(256) void k_list_row(SysConst c, SysPtrs p, int cur) {
   if (p.ctl->rebuild == 0) return;
   __shared__ float s_cs2[kMaxPairs];
   __shared__ int s_ring[4][kRing][64];
@@ -1454,7 +1527,7 @@ constexpr int kCellStage = 128;  // list entries per particle staged in LDS
 // own slots).  The lists are staged in LDS as [particle][entry] and then written out
 // by the workgroup in address order, so each entry index of the column-major list is
 // one contiguous span; entries past kCellStage are written directly.
-__global__ __launch_bounds__(128) void k_list_cell(SysConst c, SysPtrs p, int cur) {
+static __global__ __launch_bounds__(128) void k_list_cell(SysConst c, SysPtrs p, int cur) {
   if (p.ctl->rebuild == 0) return;
   __shared__ float s_cs2[kMaxPairs];
   __shared__ int s_list[kCellSlots][kCellStage + 1];  // +1: entries of one particle fall in distinct banks
@@ -1541,12 +1614,11 @@ __global__ __launch_bounds__(1024) void k_force(SysConst c, SysPtrs p, int cur) 
   const float4 *pos = p.pos[cur];
   float fx = 0.f, fy = 0.f, fz = 0.f, u = 0.f, w = 0.f;
   float4 vo = make_float4(0.f, 0.f, 0.f, 0.f), pi = vo;
-  if (active) {
-    pi = pos[i];
-    if (t == 0) vo = p.vel[i];
-    force_lane<TP, METHOD, StepBatch<TP>::value, true>(i, t, pi, pos, (const int *)p.nbl, (const int *)p.nnb, sp, c, fx, fy,
-                                             fz, u, w);
-  }
+  const int ic = active ? i : c.n - 1;
+  pi = pos[ic];
+  if (active && t == 0) vo = p.vel[i];
+  force_lane<TP, METHOD, StepBatch<TP>::value>(ic, t, active, pi, pos, (const int *)p.nbl, (const int *)p.nnb, sp, c,
+                                               fx, fy, fz, u, w);
   fx = lane_sum<TP>(fx);
   fy = lane_sum<TP>(fy);
   fz = lane_sum<TP>(fz);
@@ -2068,8 +2140,9 @@ __global__ __launch_bounds__(1024) void k_step(SysConst c, SysPtrs p, int cur, i
   float4 vo = pi, l0 = pi, kc = pi;
   int4 im = make_int4(0, 0, 0, 0);
   double x64 = 0.0, y64 = 0.0, z64 = 0.0;
+  const int ic = active ? i : c.n - 1;
+  pi = pos[ic];
   if (active) {
-    pi = pos[i];
     if (t == 0) {
       vo = p.vel[i];
       im = p.img[i];
@@ -2081,9 +2154,9 @@ __global__ __launch_bounds__(1024) void k_step(SysConst c, SysPtrs p, int cur, i
         z64 = p.pos64[3 * i + 2];
       }
     }
-    force_lane<TP, METHOD, StepBatch<TP>::value, true>(i, t, pi, pos, (const int *)p.nbl, (const int *)p.nnb, sp, c, fx, fy,
-                                             fz, u, w);
   }
+  force_lane<TP, METHOD, StepBatch<TP>::value>(ic, t, active, pi, pos, (const int *)p.nbl, (const int *)p.nnb, sp, c,
+                                               fx, fy, fz, u, w);
   fx = lane_sum<TP>(fx);
   fy = lane_sum<TP>(fy);
   fz = lane_sum<TP>(fz);
@@ -2502,15 +2575,16 @@ __global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(k
         float4 pi = make_float4(0.f, 0.f, 0.f, 0.f);
         float4 vo = pi, l0 = pi, kc = pi;
         int4 im = make_int4(0, 0, 0, 0);
+        const int ic = active ? i : c.n - 1;
+        pi = BIG ? gload(p.pos[cur], ic) : s_dyn[ic];
         if (active) {
-          pi = BIG ? gload(p.pos[cur], i) : s_dyn[i];
           if (t == 0) {
             vo = gload(p.vel, i);
             im = gload(p.img, i);
             l0 = gload(p.last, i);
           }
-          force_lane<TP, METHOD, Batch<TP>::value, true>(i, t, pi, spos, nblg, nnbg, sp, c, fx, fy, fz, uu, w);
         }
+        force_lane<TP, METHOD, Batch<TP>::value>(ic, t, active, pi, spos, nblg, nnbg, sp, c, fx, fy, fz, uu, w);
         fx = lane_sum<TP>(fx);
         fy = lane_sum<TP>(fy);
         fz = lane_sum<TP>(fz);
@@ -2610,7 +2684,7 @@ __global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(k
 }
 
 template <int TP, bool BIG>
-static const void *multi_fn(int method) {
+const void *multi_fn(int method) {
   return method == 0 ? (const void *)k_multi<TP, 0, BIG>
          : method == 1 ? (const void *)k_multi<TP, 1, BIG>
          : method == 2 ? (const void *)k_multi<TP, 2, BIG>
@@ -2618,6 +2692,156 @@ static const void *multi_fn(int method) {
          : method == 4 ? (const void *)k_multi<TP, 4, BIG>
                        : (const void *)k_multi<TP, 5, BIG>;
 }
+
+// ---------------------------------------------------------------- start of a stepping call
+
+// One launch at the start of srmd_step: the call's trace settings go into the
+// control block, and the dynamic state the call starts from (positions, velocities,
+// last-build positions, images and ids, precision residuals and the control block
+// itself) is copied into the replay snapshot.
+static __global__ __launch_bounds__(256) void k_call_begin(SysConst c, SysPtrs p, Snapshot snap, int cur, int thermo_every,
+                                                    long long trace_cap) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i == 0) {
+    Control k = *p.ctl;
+    k.thermo_every = thermo_every;
+    k.trace_cap = trace_cap;
+    k.n_records = 0;
+    *p.ctl = k;
+    *snap.ctl = k;
+  }
+  if (i < c.n) {
+    snap.pos[i] = p.pos[cur][i];
+    snap.vel[i] = p.vel[i];
+    snap.last[i] = p.last[i];
+    snap.img[i] = p.img[i];
+    if (snap.kahan) snap.kahan[i] = p.kahan[i];
+    if (snap.pos64) {
+      snap.pos64[3 * i] = p.pos64[3 * i];
+      snap.pos64[3 * i + 1] = p.pos64[3 * i + 1];
+      snap.pos64[3 * i + 2] = p.pos64[3 * i + 2];
+    }
+  }
+}
+
+// ---------------------------------------------------------------- stateless force evaluation
+
+// Set-up of a stateless force evaluation in caller-provided scratch: the control
+// block cleared with a rebuild requested, and the caller's positions (x, y, z per
+// particle, wrapped into [-L/2, L/2) as srmd_create wraps them) and types stored in
+// original order with zero velocities, zero images and identity ids; *status
+// cleared.  A type out of range is stored as 0 with its image x counter set to 1
+// (reported by k_direct_out), so that no table lookup leaves the pair tables.
+static __global__ __launch_bounds__(256) void k_direct_init(SysConst c, SysPtrs p, const float *__restrict__ xyz,
+                                                     const int *__restrict__ type, int *status) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i == 0) {
+    Control k;
+    int *w = reinterpret_cast<int *>(&k);
+    for (int q = 0; q < (int)(sizeof(Control) / sizeof(int)); ++q) w[q] = 0;
+    k.rebuild = 1;
+    *p.ctl = k;
+    *status = 0;
+  }
+  if (i >= c.n) return;
+  float r[3];
+  for (int d = 0; d < 3; ++d) {
+    const double x = (double)xyz[3 * i + d], L = c.Ld[d];
+    float f = (float)(x - L * floor(x / L + 0.5));
+    if (f >= c.halfL[d]) f -= c.L[d];
+    if (f < -c.halfL[d]) f += c.L[d];
+    r[d] = f;
+  }
+  int ty = type[i];
+  const int bad = (ty < 0 || ty >= c.ntypes) ? 1 : 0;
+  if (bad) ty = 0;
+  p.pos[0][i] = make_float4(r[0], r[1], r[2], __int_as_float(ty));
+  p.vel[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  p.img[i] = make_int4(bad, 0, 0, i);
+}
+
+// End of a stateless force evaluation: forces in original particle order, the
+// float64 potential energy and virial, and into *status the control block's error
+// bits (bit 0 non-finite force, bit 1 list capacity exceeded) and bit 2 for a type
+// out of range.
+static __global__ __launch_bounds__(256) void k_direct_out(SysConst c, SysPtrs p, float *__restrict__ force,
+                                                    double *__restrict__ energy, int *status) {
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t == 0) {
+    energy[0] = p.thermo->pe;
+    energy[1] = p.thermo->virial;
+    const int e = p.ctl->error & 3;
+    if (e) atomicOr(status, e);
+  }
+  if (t >= c.n) return;
+  const int4 im = p.img[t];
+  if (im.x != 0) atomicOr(status, 4);
+  const int id = im.w;
+  if (id < 0 || id >= c.n) return;
+  const float4 f = p.force[t];
+  force[3 * id] = f.x;
+  force[3 * id + 1] = f.y;
+  force[3 * id + 2] = f.z;
+}
+
+// ---------------------------------------------------------------- launchers
+
+template <int TP>
+hipError_t launch_step_tp(int method, int prec, dim3 g, dim3 b, hipStream_t st, const SysConst &c,
+                                 const SysPtrs &p, int cur, int tail, size_t lds) {
+#define SRMD_STEP_CASE(M, P)                                                   \
+  if (method == M && prec == P) {                                              \
+    hipLaunchKernelGGL((k_step<TP, M, P>), g, b, lds, st, c, p, cur, tail);    \
+    return hipGetLastError();                                                  \
+  }
+  SRMD_STEP_CASE(0, 0) SRMD_STEP_CASE(0, 1) SRMD_STEP_CASE(0, 2)
+  SRMD_STEP_CASE(1, 0) SRMD_STEP_CASE(1, 1) SRMD_STEP_CASE(1, 2)
+  SRMD_STEP_CASE(2, 0) SRMD_STEP_CASE(2, 1) SRMD_STEP_CASE(2, 2)
+  SRMD_STEP_CASE(3, 0) SRMD_STEP_CASE(3, 1) SRMD_STEP_CASE(3, 2)
+  SRMD_STEP_CASE(4, 0) SRMD_STEP_CASE(4, 1) SRMD_STEP_CASE(4, 2)
+  SRMD_STEP_CASE(5, 0) SRMD_STEP_CASE(5, 1) SRMD_STEP_CASE(5, 2)
+#undef SRMD_STEP_CASE
+  return hipErrorInvalidValue;
+}
+
+template <int TP>
+hipError_t launch_force_tp(int method, dim3 g, dim3 b, hipStream_t st, const SysConst &c, const SysPtrs &p,
+                                  int cur) {
+  if (method == 0) hipLaunchKernelGGL((k_force<TP, 0>), g, b, 0, st, c, p, cur);
+  else if (method == 1) hipLaunchKernelGGL((k_force<TP, 1>), g, b, 0, st, c, p, cur);
+  else if (method == 2) hipLaunchKernelGGL((k_force<TP, 2>), g, b, 0, st, c, p, cur);
+  else if (method == 3) hipLaunchKernelGGL((k_force<TP, 3>), g, b, 0, st, c, p, cur);
+  else if (method == 4) hipLaunchKernelGGL((k_force<TP, 4>), g, b, 0, st, c, p, cur);
+  else if (method == 5) hipLaunchKernelGGL((k_force<TP, 5>), g, b, 0, st, c, p, cur);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+// The templated kernels are compiled once per threads-per-particle value in a
+// translation unit of their own (this file with SRMD_TP defined), everything else in
+// the one without it.
+#define SRMD_KERNELS_OF(PREFIX, TP)                                                                                     \
+  PREFIX template hipError_t launch_step_tp<TP>(int, int, dim3, dim3, hipStream_t, const SysConst &, const SysPtrs &,   \
+                                                int, int, size_t);                                                      \
+  PREFIX template hipError_t launch_force_tp<TP>(int, dim3, dim3, hipStream_t, const SysConst &, const SysPtrs &, int); \
+  PREFIX template const void *multi_fn<TP, false>(int);
+#ifdef SRMD_TP
+SRMD_KERNELS_OF(, SRMD_TP)
+#if SRMD_TP <= 8
+template const void *multi_fn<SRMD_TP, true>(int);
+#endif
+#else
+SRMD_KERNELS_OF(extern, 1)
+SRMD_KERNELS_OF(extern, 2)
+SRMD_KERNELS_OF(extern, 4)
+SRMD_KERNELS_OF(extern, 8)
+SRMD_KERNELS_OF(extern, 16)
+SRMD_KERNELS_OF(extern, 32)
+SRMD_KERNELS_OF(extern, 64)
+extern template const void *multi_fn<1, true>(int);
+extern template const void *multi_fn<2, true>(int);
+extern template const void *multi_fn<4, true>(int);
+extern template const void *multi_fn<8, true>(int);
 
 // The persistent kernel for (tp, method); the large-system form exists for tp <= 8.
 static const void *multi_fn_of(int tp, int method, bool big) {
@@ -2691,99 +2915,6 @@ int batch_max_particles() { return kSmallN; }
 // Dynamic LDS of the large-system persistent kernel: the list build's candidate windows.
 size_t big_lds_bytes() { return 4 * (size_t)(kBatchWaves * kWaveCand); }
 
-// ---------------------------------------------------------------- start of a stepping call
-
-// One launch at the start of srmd_step: the call's trace settings go into the
-// control block, and the dynamic state the call starts from (positions, velocities,
-// last-build positions, images and ids, precision residuals and the control block
-// itself) is copied into the replay snapshot.
-__global__ __launch_bounds__(256) void k_call_begin(SysConst c, SysPtrs p, Snapshot snap, int cur, int thermo_every,
-                                                    long long trace_cap) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 0) {
-    Control k = *p.ctl;
-    k.thermo_every = thermo_every;
-    k.trace_cap = trace_cap;
-    k.n_records = 0;
-    *p.ctl = k;
-    *snap.ctl = k;
-  }
-  if (i < c.n) {
-    snap.pos[i] = p.pos[cur][i];
-    snap.vel[i] = p.vel[i];
-    snap.last[i] = p.last[i];
-    snap.img[i] = p.img[i];
-    if (snap.kahan) snap.kahan[i] = p.kahan[i];
-    if (snap.pos64) {
-      snap.pos64[3 * i] = p.pos64[3 * i];
-      snap.pos64[3 * i + 1] = p.pos64[3 * i + 1];
-      snap.pos64[3 * i + 2] = p.pos64[3 * i + 2];
-    }
-  }
-}
-
-// ---------------------------------------------------------------- stateless force evaluation
-
-// Set-up of a stateless force evaluation in caller-provided scratch: the control
-// block cleared with a rebuild requested, and the caller's positions (x, y, z per
-// particle, wrapped into [-L/2, L/2) as srmd_create wraps them) and types stored in
-// original order with zero velocities, zero images and identity ids; *status
-// cleared.  A type out of range is stored as 0 with its image x counter set to 1
-// (reported by k_direct_out), so that no table lookup leaves the pair tables.
-__global__ __launch_bounds__(256) void k_direct_init(SysConst c, SysPtrs p, const float *__restrict__ xyz,
-                                                     const int *__restrict__ type, int *status) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 0) {
-    Control k;
-    int *w = reinterpret_cast<int *>(&k);
-    for (int q = 0; q < (int)(sizeof(Control) / sizeof(int)); ++q) w[q] = 0;
-    k.rebuild = 1;
-    *p.ctl = k;
-    *status = 0;
-  }
-  if (i >= c.n) return;
-  float r[3];
-  for (int d = 0; d < 3; ++d) {
-    const double x = (double)xyz[3 * i + d], L = c.Ld[d];
-    float f = (float)(x - L * floor(x / L + 0.5));
-    if (f >= c.halfL[d]) f -= c.L[d];
-    if (f < -c.halfL[d]) f += c.L[d];
-    r[d] = f;
-  }
-  int ty = type[i];
-  const int bad = (ty < 0 || ty >= c.ntypes) ? 1 : 0;
-  if (bad) ty = 0;
-  p.pos[0][i] = make_float4(r[0], r[1], r[2], __int_as_float(ty));
-  p.vel[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-  p.img[i] = make_int4(bad, 0, 0, i);
-}
-
-// End of a stateless force evaluation: forces in original particle order, the
-// float64 potential energy and virial, and into *status the control block's error
-// bits (bit 0 non-finite force, bit 1 list capacity exceeded) and bit 2 for a type
-// out of range.
-__global__ __launch_bounds__(256) void k_direct_out(SysConst c, SysPtrs p, float *__restrict__ force,
-                                                    double *__restrict__ energy, int *status) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t == 0) {
-    energy[0] = p.thermo->pe;
-    energy[1] = p.thermo->virial;
-    const int e = p.ctl->error & 3;
-    if (e) atomicOr(status, e);
-  }
-  if (t >= c.n) return;
-  const int4 im = p.img[t];
-  if (im.x != 0) atomicOr(status, 4);
-  const int id = im.w;
-  if (id < 0 || id >= c.n) return;
-  const float4 f = p.force[t];
-  force[3 * id] = f.x;
-  force[3 * id + 1] = f.y;
-  force[3 * id + 2] = f.z;
-}
-
-// ---------------------------------------------------------------- launchers
-
 hipError_t launch_direct_init(hipStream_t st, const SysConst &c, const SysPtrs &p, const float *xyz, const int *type,
                               int *status) {
   hipLaunchKernelGGL(k_direct_init, dim3((c.n + 255) / 256), dim3(256), 0, st, c, p, xyz, type, status);
@@ -2799,37 +2930,6 @@ hipError_t launch_direct_out(hipStream_t st, const SysConst &c, const SysPtrs &p
 hipError_t launch_call_begin(hipStream_t st, const SysConst &c, const SysPtrs &p, const Snapshot &snap, int cur,
                              int thermo_every, long long trace_cap) {
   hipLaunchKernelGGL(k_call_begin, dim3((c.n + 255) / 256), dim3(256), 0, st, c, p, snap, cur, thermo_every, trace_cap);
-  return hipGetLastError();
-}
-
-template <int TP>
-static hipError_t launch_step_tp(int method, int prec, dim3 g, dim3 b, hipStream_t st, const SysConst &c,
-                                 const SysPtrs &p, int cur, int tail, size_t lds) {
-#define SRMD_STEP_CASE(M, P)                                                   \
-  if (method == M && prec == P) {                                              \
-    hipLaunchKernelGGL((k_step<TP, M, P>), g, b, lds, st, c, p, cur, tail);    \
-    return hipGetLastError();                                                  \
-  }
-  SRMD_STEP_CASE(0, 0) SRMD_STEP_CASE(0, 1) SRMD_STEP_CASE(0, 2)
-  SRMD_STEP_CASE(1, 0) SRMD_STEP_CASE(1, 1) SRMD_STEP_CASE(1, 2)
-  SRMD_STEP_CASE(2, 0) SRMD_STEP_CASE(2, 1) SRMD_STEP_CASE(2, 2)
-  SRMD_STEP_CASE(3, 0) SRMD_STEP_CASE(3, 1) SRMD_STEP_CASE(3, 2)
-  SRMD_STEP_CASE(4, 0) SRMD_STEP_CASE(4, 1) SRMD_STEP_CASE(4, 2)
-  SRMD_STEP_CASE(5, 0) SRMD_STEP_CASE(5, 1) SRMD_STEP_CASE(5, 2)
-#undef SRMD_STEP_CASE
-  return hipErrorInvalidValue;
-}
-
-template <int TP>
-static hipError_t launch_force_tp(int method, dim3 g, dim3 b, hipStream_t st, const SysConst &c, const SysPtrs &p,
-                                  int cur) {
-  if (method == 0) hipLaunchKernelGGL((k_force<TP, 0>), g, b, 0, st, c, p, cur);
-  else if (method == 1) hipLaunchKernelGGL((k_force<TP, 1>), g, b, 0, st, c, p, cur);
-  else if (method == 2) hipLaunchKernelGGL((k_force<TP, 2>), g, b, 0, st, c, p, cur);
-  else if (method == 3) hipLaunchKernelGGL((k_force<TP, 3>), g, b, 0, st, c, p, cur);
-  else if (method == 4) hipLaunchKernelGGL((k_force<TP, 4>), g, b, 0, st, c, p, cur);
-  else if (method == 5) hipLaunchKernelGGL((k_force<TP, 5>), g, b, 0, st, c, p, cur);
-  else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
@@ -2918,5 +3018,7 @@ hipError_t launch_rebuild(hipStream_t st, const SysConst &c, const SysPtrs &p, i
   }
   return hipGetLastError();
 }
+
+#endif  // SRMD_TP
 
 }  // namespace srmd

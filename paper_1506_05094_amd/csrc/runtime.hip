@@ -392,6 +392,8 @@ srmd_status fill_const(srmd_system *s) {
     c.invL[k] = (float)(1.0 / (double)s->Lf[k]);
     c.halfL[k] = 0.5f * s->Lf[k];
     c.Ld[k] = (double)s->Lf[k];
+    // the force cutoff with a margin for the float32 rounding of coordinates and distances
+    c.inner[k] = (float)(0.5 * c.Ld[k] - rcm * (1.0 + 1e-4) - 1e-6 * c.Ld[k]);
     V *= c.Ld[k];
     if (!(reach < 0.5 * c.Ld[k]))
       return fail(s, SRMD_EINVAL, "cutoff + skin must stay below half of every box side");

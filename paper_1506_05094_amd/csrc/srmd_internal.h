@@ -56,6 +56,7 @@ struct SysConst {
   float L[3];    // float32 box sides
   float invL[3]; // (float)(1.0 / (double)L)
   float halfL[3];
+  float inner[3]; // a particle with |x| below it is farther than every force cutoff from that axis's faces
   float cscale[3]; // nc / L (float32), cell coordinate scale
   double Ld[3];    // (double)L
   float dt;        // time step (float32)
