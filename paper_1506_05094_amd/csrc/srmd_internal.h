@@ -156,6 +156,16 @@ struct Snapshot {
   Control *ctl;
 };
 
+// Device arrays of a state transfer in the caller's order (particle id), x, y, z per
+// particle; an array that is not wanted is nullptr.  bad is set when an id is not one.
+struct StateXfer {
+  float *pos, *vel;
+  int *image;
+  float *force;
+  double *pos64;
+  int *bad;
+};
+
 // One system of a persistent launch: its constants, its device arrays, the position
 // buffer in use at the launch and the shape of its single-system step launch.
 struct ReplicaDesc {
