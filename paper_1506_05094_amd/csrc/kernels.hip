@@ -88,17 +88,56 @@ __device__ __forceinline__ void cell_coords(const float4 r, const SysConst &c, i
 // consecutive particles' groups follow each other, so the tp lanes of a wave that
 // serve consecutive particles read one contiguous span per iteration.  tp = 1 is
 // the paper's column-major layout (section 5).
-__device__ __forceinline__ long long nbl_addr(int i, int k, int tp, int nvp) {
-  return (long long)(k / tp) * ((long long)nvp * tp) + (long long)i * tp + (k % tp);
+__device__ __forceinline__ long long nbl_addr(int i, int k, const SysConst &c) {
+  return ((long long)(k >> c.tp_shift) * c.nvp + i) * c.tp + (k & (c.tp - 1));
+}
+
+// Linear index of cell (x, y, z): the order of the spatial sort.  Small systems:
+// row-major, x fastest.  Large systems: the grid is cut into columns of about 5 x 5
+// cells along z; the columns follow each other in a serpentine over (x, y), each is
+// traversed along z (up and down in turn) layer by layer, and a layer row by row.
+// Consecutive particles then form slabs of a column, so that the neighbourhood of a
+// few hundred of them is small enough for LDS (256 particles of the LJ liquid: about
+// 1800 particles; a stretch of x-rows of the row-major order: 4300).  A row of cells
+// along x inside one tile stays consecutive.
+struct Tile {
+  int t, x0, w;  // tile index, first cell and width along an axis
+};
+
+__device__ __forceinline__ Tile tile_of(const SysConst &c, int axis, int x) {
+  Tile r{0, 0, c.nc[axis]};
+  if (c.tiles[axis] > 1) {
+    const int q = c.tile_q[axis], rem = c.tile_rem[axis], wide = rem * (q + 1);
+    r.t = x < wide ? (x * c.tile_mq1[axis]) >> 16 : rem + (((x - wide) * c.tile_mq[axis]) >> 16);
+    r.x0 = r.t * q + min(r.t, rem);
+    r.w = q + (r.t < rem ? 1 : 0);
+  }
+  return r;
+}
+
+// Position of a column in the serpentine.
+__device__ __forceinline__ int column_seq(const SysConst &c, int tx, int ty) {
+  return ty * c.tiles[0] + ((ty & 1) ? c.tiles[0] - 1 - tx : tx);
+}
+
+__device__ __forceinline__ int cell_id(const SysConst &c, int x, int y, int z) {
+  const int nx = c.nc[0], ny = c.nc[1], nz = c.nc[2];
+  if (c.tiles[0] == 1 && c.tiles[1] == 1) return (z * ny + y) * nx + x;
+  const Tile X = tile_of(c, 0, x), Y = tile_of(c, 1, y);
+  const int before = (Y.t & 1) ? nx - X.x0 - X.w : X.x0;  // cells along x of the columns before it in its row of tiles
+  const int zz = (column_seq(c, X.t, Y.t) & 1) ? nz - 1 - z : z;
+  return nz * (nx * Y.x0 + Y.w * before) + (zz * Y.w + (y - Y.x0)) * X.w + (x - X.x0);
 }
 
 // The x extent of one stencil row: up to two runs of consecutive cells
-// [a0, a1] and [b0, b1] (the second one only when the +-2 window wraps round the
-// box), in the order dx = -2 .. +2; every cell when the axis has fewer than 5.
-__device__ __forceinline__ void row_runs(int cx, int nx, bool full, int &a0, int &a1, int &b0, int &b1) {
+// [a0, a1] and [b0, b1] (the second one only when the +-2 window wraps round the box
+// or reaches into the next tile of the cell order; tiles are at least 5 wide, so not
+// both), in the order dx = -2 .. +2; every cell when the axis has fewer than 5.
+__device__ __forceinline__ void row_runs(const SysConst &c, int cx, int &a0, int &a1, int &b0, int &b1) {
+  const int nx = c.nc[0];
   b0 = 0;
   b1 = -1;
-  if (full) {
+  if (c.full_axis & 1) {
     a0 = 0;
     a1 = nx - 1;
     return;
@@ -117,6 +156,14 @@ __device__ __forceinline__ void row_runs(int cx, int nx, bool full, int &a0, int
   } else {
     a0 = lo;
     a1 = hi;
+    if (c.tiles[0] > 1) {
+      const Tile T = tile_of(c, 0, hi);
+      if (T.x0 > lo) {
+        a1 = T.x0 - 1;
+        b0 = T.x0;
+        b1 = hi;
+      }
+    }
   }
 }
 
@@ -360,9 +407,10 @@ __device__ __forceinline__ void lj_pair(const float4 pi, const Wide &wi, const f
   const bool in_lj = ok & (r2s < rc2);
   float r2 = r2s;
   if (IMG) {
-    dx = (float)(((double)pj.x - wi.x) - (double)mx * c.Ld[0]);
-    dy = (float)(((double)pj.y - wi.y) - (double)my * c.Ld[1]);
-    dz = (float)(((double)pj.z - wi.z) - (double)mz * c.Ld[2]);
+    // (the product of an image integer and the float32 side is exact in float64)
+    dx = (float)__builtin_fma(-(double)mx, c.Ld[0], (double)pj.x - wi.x);
+    dy = (float)__builtin_fma(-(double)my, c.Ld[1], (double)pj.y - wi.y);
+    dz = (float)__builtin_fma(-(double)mz, c.Ld[2], (double)pj.z - wi.z);
     r2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
   }
   const float inv_r2 = __builtin_amdgcn_rcpf(r2);
@@ -590,8 +638,9 @@ __device__ __forceinline__ int wave_max_i32(int v) {
 // (clamped to the capacity n_max / TP of a lane), so the length and the first indices
 // share a round trip.  A wave whose particles are all farther than the cutoff from
 // every face takes the loop without image arithmetic, and a system of one type the
-// loop with scalar constants (25 and 20 instructions of about 60 per pair).
-template <int TP, int METHOD, int B, class IdxPtr>
+// loop with scalar constants (25 and 20 instructions of about 60 per pair).  SLIM: the
+// general loop only (the rare unstaged units of the staged kernels).
+template <int TP, int METHOD, int B, bool SLIM, class IdxPtr>
 __device__ __forceinline__ void force_lane(int i, int t, bool active, const float4 pi, const float4 *__restrict__ pos,
                                            IdxPtr nbl, IdxPtr nnb, const SharedPairs &sp, const SysConst &c,
                                            float &fx, float &fy, float &fz, float &u, float &w) {
@@ -617,7 +666,7 @@ __device__ __forceinline__ void force_lane(int i, int t, bool active, const floa
   }
   // from 16 lanes per particle the wave at a face sets the pace of the step: one form
   const bool near = TP >= 16 || fabsf(pi.x) >= c.inner[0] || fabsf(pi.y) >= c.inner[1] || fabsf(pi.z) >= c.inner[2];
-  if constexpr (METHOD <= 3) {
+  if constexpr (METHOD <= 3 && !SLIM) {
     if (c.ntypes == 1 && METHOD != 3) {
       if (TP >= 16 || __any(near))
         force_loop<TP, METHOD, B, true, true>(i, pi, pos, row, stride, mine, wmax, j, sp, c, fx, fy, fz, u, w);
@@ -631,6 +680,139 @@ __device__ __forceinline__ void force_lane(int i, int t, bool active, const floa
     }
   } else {
     force_loop<TP, METHOD, B, true, false>(i, pi, pos, row, stride, mine, wmax, j, sp, c, fx, fy, fz, u, w);
+  }
+}
+
+// Least of the lanes' values (at most 1e30), uniform.
+__device__ __forceinline__ float wave_min_f32(float v) {
+  auto dn = [](float a, unsigned b) { return fminf(a, __uint_as_float(b)); };
+  const unsigned id = __float_as_uint(1e30f);
+  v = dn(v, dpp32<kDppXor1, 0xF>(id, __float_as_uint(v)));
+  v = dn(v, dpp32<kDppXor2, 0xF>(id, __float_as_uint(v)));
+  v = dn(v, dpp32<kDppHalfMirror, 0xF>(id, __float_as_uint(v)));
+  v = dn(v, dpp32<kDppMirror, 0xF>(id, __float_as_uint(v)));
+  v = dn(v, dpp32<kDppBcast15, 0xA>(id, __float_as_uint(v)));
+  v = dn(v, dpp32<kDppBcast31, 0xC>(id, __float_as_uint(v)));
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
+// ---- staged lists in the force loop (large systems)
+
+// The copies of a workgroup's units' regions into LDS (unit after unit, place 0 of each
+// a far-away particle that no distance test passes).  Returns the first place of the
+// calling wave's unit, or -1 when its lists are plain ones (a region that was too large
+// for the list build, or for what the units before it leave of the LDS).  Every thread
+// of the block must call it; a barrier must follow.
+template <int TP>
+__device__ __forceinline__ int stage_fill(const SysConst &c, const SysPtrs &p, const float4 *__restrict__ pos, int lb,
+                                          float4 *s_region) {
+  const int tid = threadIdx.x, nthr = blockDim.x;
+  const int ppb = nthr / TP, units = ppb / kStageSlots, u0 = lb * units;
+  const int mine = __builtin_amdgcn_readfirstlane(tid) / (TP * kStageSlots);
+  int at = 0, place = -1;
+  for (int u = 0; u < units; ++u) {
+    if ((u0 + u) * kStageSlots >= c.n) break;
+    const int n = p.stage_n[u0 + u];
+    if (n == 0 || at + n + 1 > c.stage_lds) continue;
+    if (u == mine) place = at;
+    const unsigned *src = p.stage_src + (size_t)(u0 + u) * c.stage_cap;
+    float4 *dst = s_region + at + 1;
+    if (tid == 0) s_region[at] = make_float4(1e18f, 1e18f, 1e18f, 0.f);
+    for (int k0 = tid; k0 < n; k0 += 4 * nthr) {
+      unsigned j[4];
+      float4 v[4];
+#pragma unroll
+      for (int b = 0; b < 4; ++b) j[b] = src[min(k0 + b * nthr, n - 1)];
+#pragma unroll
+      for (int b = 0; b < 4; ++b) v[b] = pos[j[b]];
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+        if (k0 + b * nthr < n) dst[k0 + b * nthr] = v[b];
+    }
+    at += n + 1;
+  }
+  return place;
+}
+
+// force_loop over a staged list: two entries per word, neighbour positions from the LDS
+// copy.  The lists are padded with place 0 up to the unit's longest, so that a loop
+// without image arithmetic needs no test for the end of a lane's list.
+template <int TP, int METHOD, bool IMG, bool ONE>
+__device__ __forceinline__ void stage_loop(const float4 pi, const float4 *region, const unsigned *row, long long stride,
+                                           int col, int mine, int words, unsigned (&j)[4], const SharedPairs &sp,
+                                           const SysConst &c, float &fx, float &fy, float &fz, float &u, float &w) {
+  const int ti = ptype(pi);
+  const int row0 = ti * c.ntypes;
+  const Wide wi = widen(pi);
+  for (int w0 = 0; w0 < words; w0 += 4) {
+    float4 q[8];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      q[2 * b] = region[j[b] & 0xffffu];
+      q[2 * b + 1] = region[j[b] >> 16];
+    }
+    if (w0 + 4 < words) {
+#pragma unroll
+      for (int b = 0; b < 4; ++b) j[b] = __builtin_nontemporal_load(row + (long long)min(w0 + 4 + b, words - 1) * stride + col);
+    }
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      if (w0 + b < words) {  // uniform
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const bool ok = (!IMG && METHOD <= 3) || 2 * (w0 + b) + h < mine;
+          if constexpr (METHOD <= 3) {
+            lj_pair<METHOD, IMG, ONE>(pi, wi, q[2 * b + h], ok, row0, sp, c, fx, fy, fz, u, w);
+          } else {
+            if (ok) pair_acc<METHOD>(pi, wi, q[2 * b + h], ti, c.ntypes, sp, c, fx, fy, fz, u, w);
+          }
+        }
+      }
+    }
+  }
+}
+
+// force_lane over a staged list: the same pairs in the same order.  The gathers from L2
+// bound force_lane (the texture-address path takes a cycle per lane: 63 % busy, and the
+// 32-bit indices are 70 % of the bytes); from LDS a neighbour costs a quarter of that
+// and an index half the bytes.  k_step at one lane per particle, 1 024 000 particles: 178
+// -> 162 us by the column order alone, 125 us with the copies (five blocks per compute
+// unit; with a third more LDS per block, four, 131 us), bound by VALU issue (78 % busy);
+// 256 000: 50.5 -> 44.5 us; at four lanes per particle, 64 000: 20.8 -> 20.4 us.
+template <int TP, int METHOD>
+__device__ __forceinline__ void force_lane_staged(int i, int t, bool active, const float4 pi, const float4 *region,
+                                                  const SysPtrs &p, const SharedPairs &sp, const SysConst &c, float &fx,
+                                                  float &fy, float &fz, float &u, float &w) {
+  const long long stride = (long long)c.nvp * TP;
+  const int lane = threadIdx.x & 63;
+  const int i0 = __builtin_amdgcn_readfirstlane(i - lane / TP) & ~(64 / TP - 1);
+  const unsigned *row = p.list16 + (long long)i0 * TP;
+  const int col = active ? lane : 0;   // lanes past the last particle read a list that was written
+  const int cap = c.n_max / (2 * TP);  // words of one lane the list can hold
+  unsigned j[4];
+#pragma unroll
+  for (int b = 0; b < 4; ++b) j[b] = __builtin_nontemporal_load(row + (long long)min(b, cap - 1) * stride + col);
+  const int nn = active ? p.nnb[i] : 0;
+  const int mine = nn > t ? (nn - t + TP - 1) / TP : 0;
+  const int words = (wave_max_i32(mine) + 1) / 2;
+  // words past the wave's longest list are not padded: no place outside the region
+#pragma unroll
+  for (int b = 0; b < 4; ++b) j[b] = b < words ? j[b] : 0u;
+  const bool near = fabsf(pi.x) >= c.inner[0] || fabsf(pi.y) >= c.inner[1] || fabsf(pi.z) >= c.inner[2];
+  if constexpr (METHOD <= 3) {
+    if (c.ntypes == 1 && METHOD != 3) {
+      if (__any(near))
+        stage_loop<TP, METHOD, true, true>(pi, region, row, stride, col, mine, words, j, sp, c, fx, fy, fz, u, w);
+      else
+        stage_loop<TP, METHOD, false, true>(pi, region, row, stride, col, mine, words, j, sp, c, fx, fy, fz, u, w);
+    } else {
+      if (__any(near))
+        stage_loop<TP, METHOD, true, false>(pi, region, row, stride, col, mine, words, j, sp, c, fx, fy, fz, u, w);
+      else
+        stage_loop<TP, METHOD, false, false>(pi, region, row, stride, col, mine, words, j, sp, c, fx, fy, fz, u, w);
+    }
+  } else {
+    stage_loop<TP, METHOD, true, false>(pi, region, row, stride, col, mine, words, j, sp, c, fx, fy, fz, u, w);
   }
 }
 
@@ -783,7 +965,7 @@ __device__ void sort_bin(const SysConst &c, const SysPtrs &p, int cur, int base,
       const float4 r = p.pos[cur][s];
       int cx, cy, cz;
       cell_coords(r, c, cx, cy, cz);
-      const unsigned cell = (unsigned)((cz * c.nc[1] + cy) * c.nc[0] + cx);
+      const unsigned cell = (unsigned)cell_id(c, cx, cy, cz);
       p.cell_of[s] = cell;
       p.slot_in_cell[s] = atomicAdd(&p.cell_count[cell], 1u);
       tile = cell >> shift;
@@ -1064,11 +1246,11 @@ __device__ __forceinline__ void stencil_runs(const SysConst &c, int cx, int cy, 
                                              unsigned &run_start, unsigned &run_len, unsigned &excl,
                                              unsigned &total) {
   const int lane = threadIdx.x & 63;
-  const int nx = c.nc[0], ny = c.nc[1], nz = c.nc[2];
+  const int ny = c.nc[1], nz = c.nc[2];
   const bool fy = c.full_axis & 2, fz = c.full_axis & 4;
   const int ny_eff = fy ? ny : 5, nz_eff = fz ? nz : 5;
   int a0, a1, b0, b1;
-  row_runs(cx, nx, c.full_axis & 1, a0, a1, b0, b1);
+  row_runs(c, cx, a0, a1, b0, b1);
   run_start = 0;
   run_len = 0;
   const int row = lane >> 1;
@@ -1076,12 +1258,12 @@ __device__ __forceinline__ void stencil_runs(const SysConst &c, int cx, int cy, 
     const int oy = row % ny_eff, oz = row / ny_eff;
     const int yy = fy ? oy : (cy + oy - 2 + ny) % ny;
     const int zz = fz ? oz : (cz + oz - 2 + nz) % nz;
-    const int rowbase = (zz * ny + yy) * nx;
     const int x0 = (lane & 1) ? b0 : a0, x1 = (lane & 1) ? b1 : a1;
     if (x1 >= x0) {
+      const int first = cell_id(c, x0, yy, zz);
       // clamped to [0, n]: a run never reaches outside the sorted arrays
-      const unsigned s1 = min(cstart[rowbase + x1 + 1], (unsigned)c.n);
-      const unsigned s0 = min(cstart[rowbase + x0], s1);
+      const unsigned s1 = min(cstart[first + (x1 - x0) + 1], (unsigned)c.n);
+      const unsigned s0 = min(cstart[first], s1);
       run_start = s0;
       run_len = s1 - s0;
     }
@@ -1145,7 +1327,7 @@ __device__ int list_wave_one(const SysConst &c, const SysPtrs &p, int cur, int t
         }
         const unsigned long long mask = __ballot(hit);
         const int k = count + __popcll(mask & ((1ull << lane) - 1ull));
-        if (hit && k < nmax) p.nbl[nbl_addr(t, k, c.tp, c.nvp)] = (int)u[cb];
+        if (hit && k < nmax) p.nbl[nbl_addr(t, k, c)] = (int)u[cb];
         count += __popcll(mask);
       }
     }
@@ -1192,7 +1374,7 @@ __device__ int list_allpairs_one(const SysConst &c, const SysPtrs &p, int i, con
       }
       const unsigned long long mask = __ballot(hit);
       const int k = count + __popcll(mask & ((1ull << lane) - 1ull));
-      if (hit && k < nmax) p.nbl[nbl_addr(i, k, c.tp, c.nvp)] = jj[cb];
+      if (hit && k < nmax) p.nbl[nbl_addr(i, k, c)] = jj[cb];
       count += __popcll(mask);
     }
   }
@@ -1271,7 +1453,7 @@ static __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
   const int lane = threadIdx.x & 63;
   int(*ring)[64] = s_ring[threadIdx.x >> 6];
   const int nmax = c.n_max;
-  const int nx = c.nc[0], ny = c.nc[1], nz = c.nc[2];
+  const int ny = c.nc[1], nz = c.nc[2];
   const bool fy = c.full_axis & 2, fz = c.full_axis & 4;
   const int ny_eff = fy ? ny : 5, nz_eff = fz ? nz : 5, nrows = ny_eff * nz_eff;
   const unsigned nu = (unsigned)c.n;
@@ -1285,42 +1467,37 @@ static __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
     int cx, cy, cz;
     cell_coords(r, c, cx, cy, cz);
     int a0, a1, b0, b1;
-    row_runs(cx, nx, c.full_axis & 1, a0, a1, b0, b1);
+    row_runs(c, cx, a0, a1, b0, b1);
     const bool two = b1 >= b0;
-    auto row_base = [&](int rr) {
+    auto bounds = [&](int rr, unsigned &ca0, unsigned &ca1, unsigned &cb0, unsigned &cb1) {
       const int oz = rr / ny_eff, oy = rr - oz * ny_eff;
       const int zz = fz ? oz : (cz + oz - 2 + nz) % nz;
       const int yy = fy ? oy : (cy + oy - 2 + ny) % ny;
-      return (zz * ny + yy) * nx;
+      const int fa = cell_id(c, a0, yy, zz);
+      ca0 = p.cell_start[fa];
+      ca1 = p.cell_start[fa + (a1 - a0) + 1];
+      if (two) {
+        const int fb = cell_id(c, b0, yy, zz);
+        cb0 = p.cell_start[fb];
+        cb1 = p.cell_start[fb + (b1 - b0) + 1];
+      }
     };
-    int rb = row_base(0);
-    unsigned ca0 = p.cell_start[rb + a0], ca1 = p.cell_start[rb + a1 + 1], cb0 = 0, cb1 = 0;
-    if (two) {
-      cb0 = p.cell_start[rb + b0];
-      cb1 = p.cell_start[rb + b1 + 1];
-    }
+    unsigned ca0, ca1, cb0 = 0, cb1 = 0;
+    bounds(0, ca0, ca1, cb0, cb1);
     int count = 0;      // entries found by this lane
     int ring_end = 0;   // this lane's entries below it are in the ring (or written)
     bool spill = false; // this lane writes its later entries directly
     int flushed = 0;    // uniform: every lane's slots below it are written
     auto flush = [&](int upto) {
       for (int k = flushed; k < upto; ++k)
-        if (act && k < ring_end && k < nmax) p.nbl[nbl_addr(t, k, c.tp, c.nvp)] = ring[k % kRing][lane];
+        if (act && k < ring_end && k < nmax) p.nbl[nbl_addr(t, k, c)] = ring[k % kRing][lane];
       flushed = upto;
     };
     for (int rr = 0; rr < nrows; ++rr) {
       // runs clamped to [0, n]: they never reach outside the sorted arrays
       const unsigned sa1 = min(ca1, nu), sa0 = min(ca0, sa1);
       const unsigned sb1 = two ? min(cb1, nu) : 0u, sb0 = two ? min(cb0, sb1) : 0u;
-      if (rr + 1 < nrows) {
-        rb = row_base(rr + 1);
-        ca0 = p.cell_start[rb + a0];
-        ca1 = p.cell_start[rb + a1 + 1];
-        if (two) {
-          cb0 = p.cell_start[rb + b0];
-          cb1 = p.cell_start[rb + b1 + 1];
-        }
-      }
+      if (rr + 1 < nrows) bounds(rr + 1, ca0, ca1, cb0, cb1);
       const unsigned la = sa1 - sa0, lt = act ? la + (sb1 - sb0) : 0u;
       for (unsigned base = 0; base < lt; base += kThreadBatch) {
         unsigned u[kThreadBatch];
@@ -1340,7 +1517,7 @@ static __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
             if (r2 < s_cs2[ti * c.ntypes + ptype(q[b])]) {
               if (!spill && count - flushed >= kRing) spill = true;
               if (spill) {
-                if (count < nmax) p.nbl[nbl_addr(t, count, c.tp, c.nvp)] = (int)u[b];
+                if (count < nmax) p.nbl[nbl_addr(t, count, c)] = (int)u[b];
               } else {
                 ring[count % kRing][lane] = (int)u[b];
                 ring_end = count + 1;
@@ -1361,6 +1538,423 @@ static __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
     kept_sum += kept;
   }
   list_tally(kept_sum, longest, nmax, p.ctl);
+}
+
+// ---- staged list build (large systems)
+
+constexpr int kStageCells = 1600;  // cells of a region at most
+constexpr int kStageTest = 4;      // candidates tested together
+constexpr int kStageLanes = 2;     // lanes per particle of the staged list build
+constexpr int kStageThreads = kStageSlots * kStageLanes;
+
+// The cells a run of sorted slots needs for its lists: a box of cells (start, may be
+// negative: periodic; extent), 2 cells wider than the slots' own box on every side.
+struct Region {
+  int x0, y0, z0, X, Y, Z;
+};
+
+// Region of the slots whose first and last lie in cells a and b (x, y, z): the tile of
+// their column and their layers; over two columns the box of both tiles (neighbours
+// in the serpentine) and the layers up to their common end; over more columns whole
+// columns (then usually too large, see k_list_stage).
+__device__ __forceinline__ Region region_of(const SysConst &c, const int (&a)[3], const int (&b)[3]) {
+  const Tile ax = tile_of(c, 0, a[0]), ay = tile_of(c, 1, a[1]), bx = tile_of(c, 0, b[0]), by = tile_of(c, 1, b[1]);
+  const int qa = column_seq(c, ax.t, ay.t), qb = column_seq(c, bx.t, by.t);
+  int zlo = min(a[2], b[2]), zhi = max(a[2], b[2]);
+  if (qb == qa + 1) {
+    if (qa & 1)
+      zlo = 0;
+    else
+      zhi = c.nc[2] - 1;
+  } else if (qb > qa + 1) {
+    zlo = 0;
+    zhi = c.nc[2] - 1;
+  }
+  const bool rows = ay.t != by.t && qb > qa + 1;  // several rows of tiles: the whole x extent
+  const int xlo = rows ? 0 : min(ax.x0, bx.x0), xhi = rows ? c.nc[0] : max(ax.x0 + ax.w, bx.x0 + bx.w);
+  const int ylo = min(ay.x0, by.x0), yhi = max(ay.x0 + ay.w, by.x0 + by.w);
+  return Region{xlo - 2, ylo - 2, zlo - 2, xhi - xlo + 4, yhi - ylo + 4, zhi - zlo + 5};
+}
+
+// The lanes of a wave exchange data through LDS: their accesses stay in program order.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The lists of one unit's particles against the LDS copy of their region.
+// IMG: the region wraps round the box, so differences take the image arithmetic
+// (otherwise every image integer is 0).  ONE: one particle type.
+struct StageView {
+  const float4 *pos;         // region's near particles from place 1 on; .w holds slot << 2 | type
+  const unsigned short *cs;  // first places of the region's cells (x fastest, then y, z)
+  unsigned short *ring;      // the wave's ring of entries, [entry][particle]
+  const float *cs2;          // list radii of the type pairs
+};
+
+// m = 2 m + (this lane's bit of mask): one instruction per candidate.
+__device__ __forceinline__ void push_bit(unsigned &m, unsigned long long mask) {
+  __asm__("v_addc_co_u32_e64 %0, vcc, %0, %0, %1" : "+v"(m) : "s"(mask) : "vcc");
+}
+
+// A staged list pairs the entries k and k + tp of one of the tp lanes in a word, so that
+// a lane reads two of its own entries at once.  Word wd holds entry stage_entry and the
+// one tp further; it is stored as word wd of the interleaved layout (nbl_addr).
+__device__ __forceinline__ int stage_entry(int wd, const SysConst &c) {
+  return (wd >> c.tp_shift << (c.tp_shift + 1)) | (wd & (c.tp - 1));
+}
+__device__ __forceinline__ long long stage_half(int i, int k, const SysConst &c) {  // of entry k, in 16-bit units
+  const int wd = (k >> (c.tp_shift + 1) << c.tp_shift) | (k & (c.tp - 1));
+  return 2 * nbl_addr(i, wd, c) + ((k >> c.tp_shift) & 1);
+}
+
+// The kStageLanes = 2 lanes of a particle take two rows of the stencil at a time, one
+// each; the second lane's hits follow the first's in the list.  (One lane per particle
+// leaves a wave alone with 25 rows of dependent LDS reads, four cost more instructions
+// around the tests than the shorter chain saves.)
+template <bool IMG, bool ONE>
+__device__ __forceinline__ int stage_lists(const SysConst &c, const SysPtrs &p, const Region &R, const StageView &v,
+                                           int t, bool act, const float4 r, int cell, int gy, int gz,
+                                           int *s_longest) {
+  // cell: the first cell of the particle's stencil in the region; gy, gz: that cell's
+  // coordinates in the box (negative or past the end: beyond the face)
+  static_assert(kStageLanes == 2, "a particle's lanes are a pair");
+  constexpr int kCols = 64 / kStageLanes;  // particles of a wave
+  const int lane = threadIdx.x & 63, sub = lane % kStageLanes, col = lane / kStageLanes;
+  const int ti = ptype(r), group = 2 * c.tp;
+  const int nmax = c.n_max;
+  // the particle's own place in the copy: its cell is the stencil's centre
+  const int centre = v.cs[cell + (2 * R.Y + 2) * R.X + 2];
+  const int self = centre + (t - (int)((unsigned)__float_as_int(v.pos[centre].w) >> 2));
+  int count = 0;      // entries of the particle (the same in its lanes)
+  int flushed = 0;    // uniform: every particle's entries below it are written (a multiple of group)
+  bool spill = false; // this particle's entries are written directly
+  auto direct = [&](int k, unsigned e) {
+    if (k < nmax) reinterpret_cast<unsigned short *>(p.list16)[stage_half(t, k, c)] = (unsigned short)e;
+  };
+  unsigned short *const ring = v.ring + col;
+  unsigned *const list = p.list16 + (long long)t * c.tp;
+  const long long stride = (long long)c.nvp * c.tp;
+  // the words of entries [flushed, upto), the particle's lanes taking turns; last: place
+  // 0 past the end of a list
+  auto flush = [&](int upto, bool last) {
+    upto = min(upto, nmax);
+    wave_lds_order();
+    for (int wd = flushed / 2 + sub; wd < upto / 2; wd += kStageLanes) {
+      const int k = stage_entry(wd, c);
+      unsigned lo = ring[((unsigned)k % kRing) * kCols], hi = ring[((unsigned)(k + c.tp) % kRing) * kCols];
+      if (last) {
+        lo = k < count ? lo : 0u;
+        hi = k + c.tp < count ? hi : 0u;
+      }
+      if (act && !spill) list[(wd >> c.tp_shift) * stride + (wd & (c.tp - 1))] = lo | hi << 16;
+    }
+    flushed = max(flushed, upto);
+    wave_lds_order();
+  };
+  int oy = sub, oz = 0;  // this lane's row
+  for (int row = 0; row < 25; row += kStageLanes) {
+    const int base = cell + (oz * R.Y + oy) * R.X;  // cell: the stencil's first cell
+    const bool mine = act && oz < 5;
+    // The image shift along y and z is the row's: a row past a face is its periodic twin
+    // (the image integer of every difference in it is then -1 or 1, else 0).
+    float sy = 0.f, sz = 0.f;
+    if (IMG) {
+      const int y = gy + oy, z = gz + oz;
+      sy = y < 0 ? -c.L[1] : y >= c.nc[1] ? c.L[1] : 0.f;
+      sz = z < 0 ? -c.L[2] : z >= c.nc[2] ? c.L[2] : 0.f;
+    }
+    const int lo = mine ? v.cs[base] : 0, n = mine ? v.cs[base + 5] - lo : 0;
+    // 32 candidates at a time (a row of 5 cells of a liquid holds about 12): the hits as
+    // bits, first candidate highest, then the entries of the set bits in order.  Longer
+    // rows are rare; the rows' further candidates would follow out of order, so the rows
+    // are then taken one after the other.
+    const bool lone = __any(n > 32);
+    for (int turn = 0; turn < (lone ? kStageLanes : 1); ++turn) {
+      const int len = lone && turn != sub ? 0 : n;
+      for (int c0 = 0; __any(c0 < len); c0 += 32) {
+        const int first = lo + c0, nc = max(0, min(len - c0, 32));
+        unsigned m = 0;
+        int b0 = 0;
+        for (; b0 < nc; b0 += kStageTest) {
+          float4 q[kStageTest];
+#pragma unroll
+          for (int b = 0; b < kStageTest; ++b) q[b] = v.pos[first + b0 + b];  // up to kStageTest - 1 past the row
+#pragma unroll
+          for (int b = 0; b < kStageTest; ++b) {
+            float dx = q[b].x - r.x, dy = q[b].y - r.y, dz = q[b].z - r.z;
+            if (IMG) {
+              dx = min_image(dx, c.L[0], c.invL[0]);
+              dy += sy;
+              dz += sz;
+            }
+            const float r2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
+            const float cut = ONE ? c.pt.cs2[0] : v.cs2[ti * c.ntypes + (__float_as_int(q[b].w) & 3)];
+            push_bit(m, __builtin_amdgcn_ballot_w64(r2 < cut));
+          }
+        }
+        // candidate k to bit 31 - k (b0 were pushed, those past nc fall out)
+        m = nc > 0 ? m >> (b0 - nc) << (32 - nc) : 0u;
+        if (oz == 2 && oy == 2 && (unsigned)(self - first) < (unsigned)nc) m &= ~(0x80000000u >> (self - first));
+        const int hits = __builtin_popcount(m), other = (int)xor_lane<1>((unsigned)hits), all = hits + other;
+        int k = count + (sub ? other : 0);
+        if (__any(!spill && count + all - flushed > kRing)) {
+          const int low = 0x3fffffff - wave_max_i32(act && !spill ? 0x3fffffff - count : 0);
+          flush(min(low & -group, flushed + kRing), false);
+          if (!spill && count + all - flushed > kRing) {
+            // far ahead of the wave's slowest particle: this list is written directly from here on
+            for (int e = flushed + sub; e < count; e += kStageLanes) direct(e, ring[((unsigned)e % kRing) * kCols]);
+            spill = true;
+          }
+        }
+        count += all;
+        if (!__any(spill)) {
+          while (m) {
+            const int b = __builtin_clz(m);
+            m &= ~(0x80000000u >> b);
+            ring[((unsigned)k % kRing) * kCols] = (unsigned short)(first + b);
+            ++k;
+          }
+        } else {
+          while (m) {
+            const int b = __builtin_clz(m);
+            m &= ~(0x80000000u >> b);
+            if (spill)
+              direct(k, (unsigned)(first + b));
+            else
+              ring[((unsigned)k % kRing) * kCols] = (unsigned short)(first + b);
+            ++k;
+          }
+        }
+      }
+    }
+    oy += kStageLanes;
+    if (oy >= 5) {
+      oy -= 5;
+      ++oz;
+    }
+  }
+  // pad every list to the unit's longest (whole groups)
+  const int longest = wave_max_i32(act ? count : 0);
+  if (lane == 0) atomicMax(s_longest, longest);
+  __syncthreads();
+  const int end = __builtin_amdgcn_readfirstlane((*s_longest + group - 1) & -group);
+  if (act && spill)
+    for (int k = count + sub; k < end; k += kStageLanes) direct(k, 0u);
+  flush(end, true);
+  return count;
+}
+
+// Dynamic LDS of the staged list build: the region's positions, its cell starts and the
+// waves' entry rings.
+__host__ __device__ inline size_t stage_list_bytes(const SysConst &c) {
+  return sizeof(float4) * (size_t)(c.stage_cap + 1 + kStageTest) + sizeof(unsigned short) * (kStageCells + 8) +
+         sizeof(unsigned short) * kRing * kStageSlots;
+}
+
+// Verlet lists of large systems for units of kStageSlots sorted slots (slabs of a column
+// of the cell order).  The workgroup copies the region of cells around its slots into
+// LDS once (the cells' first places by a prefix sum over their counts) and each
+// thread tests the candidates of its particle's 25 stencil rows, each a contiguous range
+// of the copy, in the order of the other builders, so the lists hold the same
+// particles in the same order, as 16-bit places in the copy (the step kernel makes the
+// same copy from stage_src).  Against k_list_thread (VALU issue 85 % busy: 64
+// instructions per candidate slot with its per-lane addresses and image arithmetic,
+// every candidate gathered per lane from L2) a candidate is one LDS read at a constant
+// offset and 8 instructions, as most regions do not wrap round the box: 670 -> 390 us a
+// build at 1 024 000 particles (VALU issue still all busy: 236 M instead of 326 M
+// instructions, a third of them around the tests), 190 -> 124 at 256 000, 120 -> 57 at
+// 64 000.  A unit whose region does not fit (several columns, crowded cells) gets plain
+// lists, a wave per particle, from device memory.
+static __global__ __launch_bounds__(kStageThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_list_stage(SysConst c, SysPtrs p, int cur) {
+  if (p.ctl->rebuild == 0) return;
+  extern __shared__ float4 s_pos[];
+  __shared__ float s_cs2[kMaxPairs];
+  __shared__ unsigned s_w[16];
+  __shared__ int s_longest, s_bad;
+  __shared__ float s_box[kStageThreads / 64][2][6];  // per wave, column: least x, y, z and -x, -y, -z
+  unsigned short *s_cs = reinterpret_cast<unsigned short *>(s_pos + c.stage_cap + 1 + kStageTest);
+  unsigned *s_ring = reinterpret_cast<unsigned *>(s_cs + kStageCells + 8);
+  const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, wv = tid >> 6, nw = nthr >> 6;
+  if (tid < kMaxPairs) s_cs2[tid] = c.pt.cs2[tid];
+  if (tid == 0) s_longest = s_bad = 0;
+  const int unit = xcd_remap(blockIdx.x, gridDim.x);
+  const int s0 = unit * kStageSlots, s1 = min(c.n, s0 + kStageSlots);
+  int ca[3], cb[3];
+  cell_coords(p.t_pos[s0], c, ca[0], ca[1], ca[2]);
+  cell_coords(p.t_pos[s1 - 1], c, cb[0], cb[1], cb[2]);
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {  // uniform: the region's arithmetic stays scalar
+    ca[d] = __builtin_amdgcn_readfirstlane(ca[d]);
+    cb[d] = __builtin_amdgcn_readfirstlane(cb[d]);
+  }
+  const Region R = region_of(c, ca, cb);
+  const bool straddles = tile_of(c, 0, ca[0]).t != tile_of(c, 0, cb[0]).t || tile_of(c, 1, ca[1]).t != tile_of(c, 1, cb[1]).t;
+  const int cells = R.X * R.Y * R.Z;
+  const int t = s0 + tid / kStageLanes;
+  const bool act = t < s1;
+  const int ts = act ? t : s0;
+  const float4 r = p.t_pos[ts];
+  int cx, cy, cz;
+  cell_coords(r, c, cx, cy, cz);
+  bool fits = cells <= kStageCells;
+  unsigned total = 0;
+  if (fits) {
+    // boxes of the unit's particles, one for the first column and one for the rest
+    const bool second = straddles && (tile_of(c, 0, cx).t != tile_of(c, 0, ca[0]).t || tile_of(c, 1, cy).t != tile_of(c, 1, ca[1]).t);
+    const int boxes = straddles ? 2 : 1;
+    for (int q = 0; q < boxes; ++q) {
+      const bool in = second == (q == 1);
+      const float e[6] = {r.x, r.y, r.z, -r.x, -r.y, -r.z};
+#pragma unroll
+      for (int d = 0; d < 6; ++d) {
+        const float lo = wave_min_f32(in ? e[d] : 1e30f);
+        if (lane == 0) s_box[wv][q][d] = lo;
+      }
+    }
+    __syncthreads();
+    if (tid < 6 * boxes) {
+      const int q = tid / 6, d = tid - 6 * q;
+      float lo = s_box[0][q][d];
+      for (int k = 1; k < nw; ++k) lo = fminf(lo, s_box[k][q][d]);
+      s_box[0][q][d] = lo;
+    }
+    __syncthreads();
+    // The region's cells: first slot, and a bit for each particle near enough to one of
+    // the boxes to be a neighbour (five sixths of them in the LJ liquid); both in the
+    // ring's space.  Near is judged with a margin far above its rounding.
+    unsigned *s_first = s_ring, *s_near = s_ring + kStageCells;
+    for (int k = tid; k < cells; k += nthr) {
+      const int xy = R.X * R.Y, z = k / xy, y = (k - z * xy) / R.X, x = k - z * xy - y * R.X;
+      // cells past a face are their periodic twins, the particles shifted by the side
+      float shift[3];
+      auto wrap = [&](int v, int d) {
+        const int n = c.nc[d], out = v < 0 ? -1 : v >= n ? 1 : 0;
+        shift[d] = (float)out * c.L[d];
+        return v - out * n;
+      };
+      const int gx = wrap(R.x0 + x, 0), gy = wrap(R.y0 + y, 1), gz = wrap(R.z0 + z, 2);
+      const int id = cell_id(c, gx, gy, gz);
+      const unsigned e = min(p.cell_start[id + 1], (unsigned)c.n), f = min(p.cell_start[id], e), cnt = e - f;
+      if (cnt > 32) s_bad = 1;
+      auto is_near = [&](const float4 v) {
+        const float px = v.x + shift[0], py = v.y + shift[1], pz = v.z + shift[2];
+        auto dist = [&](const float *bx) {
+          const float dx = fmaxf(0.f, fmaxf(bx[0] - px, px + bx[3])), dy = fmaxf(0.f, fmaxf(bx[1] - py, py + bx[4])),
+                      dz = fmaxf(0.f, fmaxf(bx[2] - pz, pz + bx[5]));
+          return dx * dx + dy * dy + dz * dz;
+        };
+        float d2 = dist(s_box[0][0]);
+        if (straddles) d2 = fminf(d2, dist(s_box[0][1]));
+        return d2 < c.stage_reach2 ? 1u : 0u;
+      };
+      unsigned near = 0;
+      for (unsigned e0 = 0; e0 < min(cnt, 32u); e0 += 4) {
+        const unsigned l = cnt - 1;
+        const float4 v0 = p.t_pos[f + e0], v1 = p.t_pos[f + min(e0 + 1, l)], v2 = p.t_pos[f + min(e0 + 2, l)],
+                     v3 = p.t_pos[f + min(e0 + 3, l)];
+        near |= (is_near(v0) | is_near(v1) << 1 | is_near(v2) << 2 | is_near(v3) << 3) << e0;
+      }
+      if (cnt < 32) near &= (1u << cnt) - 1u;
+      s_first[k] = f;
+      s_near[k] = near;
+      s_cs[k] = (unsigned short)__builtin_popcount(near);
+    }
+    __syncthreads();
+    // exclusive scan of the counts, consecutive cells per thread
+    const int per = (cells + nthr - 1) / nthr, k0 = min(cells, tid * per), k1 = min(cells, k0 + per);
+    unsigned sum = 0;
+    for (int k = k0; k < k1; ++k) sum += s_cs[k];
+    const unsigned incl = wave_incl_scan(sum);
+    if (lane == 63) s_w[wv] = incl;
+    __syncthreads();
+    unsigned at = incl - sum;
+    for (int k = 0; k < nw; ++k) {
+      if (k < wv) at += s_w[k];
+      total += s_w[k];
+    }
+    fits = total <= (unsigned)c.stage_cap && s_bad == 0;
+    if (fits) {
+      // each particle's source slot into its place, then the particles themselves
+      for (int k = k0; k < k1; ++k) {
+        unsigned near = s_near[k];
+        const unsigned f = s_first[k];
+        s_cs[k] = (unsigned short)(at + 1);
+        while (near) {
+          const int e = __builtin_ctz(near);
+          near &= near - 1;
+          s_pos[++at].w = __int_as_float((int)(f + e));
+        }
+      }
+      if (tid == 0) s_cs[cells] = (unsigned short)(total + 1);
+      __syncthreads();
+      unsigned *src_out = p.stage_src + (size_t)unit * c.stage_cap;
+      for (unsigned q0 = tid; q0 < total; q0 += 4 * nthr) {
+        float4 v[4];
+        unsigned src[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          const unsigned q = q0 + b * nthr;
+          src[b] = q < total ? (unsigned)__float_as_int(s_pos[q + 1].w) : (unsigned)s0;
+          v[b] = p.t_pos[src[b]];
+        }
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          const unsigned q = q0 + b * nthr;
+          if (q < total) {
+            src_out[q] = src[b];
+            v[b].w = __int_as_float((int)(src[b] << 2 | (unsigned)ptype(v[b])));
+            s_pos[q + 1] = v[b];
+          }
+        }
+      }
+    }
+  }
+  __syncthreads();
+  if (tid == 0) p.stage_n[unit] = fits ? (int)total : 0;
+  if (act && tid % kStageLanes == 0) place_sorted(p, cur, t, r);
+  int kept = 0, longest = 0;
+  if (fits) {
+    const int cell = ((cz - R.z0 - 2) * R.Y + (cy - R.y0 - 2)) * R.X + (cx - R.x0 - 2);
+    const StageView v{s_pos, s_cs, reinterpret_cast<unsigned short *>(s_ring) + wv * kRing * (64 / kStageLanes), s_cs2};
+    const bool img = R.x0 < 0 || R.y0 < 0 || R.z0 < 0 || R.x0 + R.X > c.nc[0] || R.y0 + R.Y > c.nc[1] || R.z0 + R.Z > c.nc[2];
+    const int count = c.ntypes == 1 ? (img ? stage_lists<true, true>(c, p, R, v, ts, act, r, cell, cy - 2, cz - 2, &s_longest)
+                                           : stage_lists<false, true>(c, p, R, v, ts, act, r, cell, cy - 2, cz - 2, &s_longest))
+                                    : (img ? stage_lists<true, false>(c, p, R, v, ts, act, r, cell, cy - 2, cz - 2, &s_longest)
+                                           : stage_lists<false, false>(c, p, R, v, ts, act, r, cell, cy - 2, cz - 2, &s_longest));
+    longest = act ? count : 0;
+    if (act && tid % kStageLanes == 0) {
+      kept = min(count, c.n_max);
+      p.nnb[t] = kept;
+    }
+  } else {
+    unsigned *cand = reinterpret_cast<unsigned *>(s_pos) + wv * kWaveCand;
+    const int fw = min(nw, (int)(stage_list_bytes(c) / (sizeof(unsigned) * kWaveCand)));  // waves whose windows fit
+    for (int q = s0 + wv; wv < fw && q < s1; q += fw) {
+      const int k = list_wave_one<false>(c, p, cur, q, cand, s_cs2, p.t_pos, p.cell_start, longest);
+      if (lane == 0) kept += k;
+    }
+  }
+  list_tally(kept, longest, c.n_max, p.ctl);
+}
+
+// The staged lists as plain ones (slot indices in nbl), for what reads those: pairs and
+// states read back, the persistent kernel.  drop: the units' lists are plain from now on.
+static __global__ __launch_bounds__(kStageSlots) void k_stage_expand(SysConst c, SysPtrs p, int drop) {
+  const int unit = blockIdx.x, i = unit * kStageSlots + threadIdx.x;
+  const int n = p.stage_n[unit];
+  if (n > 0 && i < c.n) {
+    const unsigned *src = p.stage_src + (size_t)unit * c.stage_cap;
+    const unsigned short *list = reinterpret_cast<const unsigned short *>(p.list16);
+    const int nn = p.nnb[i];
+    for (int k = 0; k < nn; ++k) {
+      const int e = list[stage_half(i, k, c)];
+      p.nbl[nbl_addr(i, k, c)] = (int)src[min(max(e - 1, 0), n - 1)];
+    }
+  }
+  __syncthreads();
+  if (drop && threadIdx.x == 0) p.stage_n[unit] = 0;
 }
 
 // Row-staged list build (list mode 5): one workgroup per x-row of cells.  The
@@ -1404,13 +1998,13 @@ static __global__ __launch_bounds__(256) void k_list_row(SysConst c, SysPtrs p, 
     int cx, cyy, czz;
     cell_coords(r, c, cx, cyy, czz);
     int a0, a1, b0, b1;
-    row_runs(cx, nx, c.full_axis & 1, a0, a1, b0, b1);
+    row_runs(c, cx, a0, a1, b0, b1);
     const bool two = b1 >= b0;
     int count = 0, ring_end = 0, flushed = 0;
     bool spill = false;
     auto flush = [&](int upto) {
       for (int k = flushed; k < upto; ++k)
-        if (act && k < ring_end && k < nmax) p.nbl[nbl_addr(t, k, c.tp, c.nvp)] = ring[k % kRing][lane];
+        if (act && k < ring_end && k < nmax) p.nbl[nbl_addr(t, k, c)] = ring[k % kRing][lane];
       flushed = upto;
     };
     for (int rr = 0; rr < nrows; ++rr) {
@@ -1438,7 +2032,7 @@ static __global__ __launch_bounds__(256) void k_list_row(SysConst c, SysPtrs p, 
         if (r2 < s_cs2[ti * c.ntypes + ptype(q)]) {
           if (!spill && count - flushed >= kRing) spill = true;
           if (spill) {
-            if (count < nmax) p.nbl[nbl_addr(t, count, c.tp, c.nvp)] = (int)u;
+            if (count < nmax) p.nbl[nbl_addr(t, count, c)] = (int)u;
           } else {
             ring[count % kRing][lane] = (int)u;
             ring_end = count + 1;
@@ -1566,7 +2160,7 @@ static __global__ __launch_bounds__(128) void k_list_cell(SysConst c, SysPtrs p,
     if (k < kCellStage)
       s_list[i - T0][k] = j;
     else if (k < nmax)
-      p.nbl[nbl_addr(i, k, c.tp, c.nvp)] = j;
+      p.nbl[nbl_addr(i, k, c)] = j;
   };
   for (int sg = wv; sg < nseg; sg += 2) {
     const int l0 = s_seg[sg], l1 = s_seg[sg + 1];
@@ -1600,14 +2194,17 @@ static __global__ __launch_bounds__(128) void k_list_cell(SysConst c, SysPtrs p,
 
 // ---------------------------------------------------------------- force only
 
-template <int TP, int METHOD>
+template <int TP, int METHOD, bool STAGE>
 __global__ __launch_bounds__(1024) void k_force(SysConst c, SysPtrs p, int cur) {
+  extern __shared__ float4 s_region[];
   __shared__ SharedPairs sp;
   __shared__ BlockPartial s_waves[16];
   const unsigned long long tstart = wall_clock64();
   stage_pairs(sp, c);
-  __syncthreads();
   const int lb = xcd_remap(blockIdx.x, gridDim.x);
+  int place = -1;
+  if constexpr (STAGE) place = stage_fill<TP>(c, p, p.pos[cur], lb, s_region);
+  __syncthreads();
   const int gt = lb * blockDim.x + threadIdx.x;
   const int i = gt / TP, t = gt % TP;
   const bool active = i < c.n;
@@ -1617,8 +2214,11 @@ __global__ __launch_bounds__(1024) void k_force(SysConst c, SysPtrs p, int cur) 
   const int ic = active ? i : c.n - 1;
   pi = pos[ic];
   if (active && t == 0) vo = p.vel[i];
-  force_lane<TP, METHOD, StepBatch<TP>::value>(ic, t, active, pi, pos, (const int *)p.nbl, (const int *)p.nnb, sp, c,
-                                               fx, fy, fz, u, w);
+  if (STAGE && place >= 0)
+    force_lane_staged<TP, METHOD>(ic, t, active, pi, s_region + place, p, sp, c, fx, fy, fz, u, w);
+  else
+    force_lane<TP, METHOD, StepBatch<TP>::value, STAGE>(ic, t, active, pi, pos, (const int *)p.nbl, (const int *)p.nnb, sp,
+                                                        c, fx, fy, fz, u, w);
   fx = lane_sum<TP>(fx);
   fy = lane_sum<TP>(fy);
   fz = lane_sum<TP>(fz);
@@ -2084,9 +2684,17 @@ __device__ void step_tail(const SysConst &c, const SysPtrs &p, int G, int next, 
 
 // ---------------------------------------------------------------- fused step
 
-template <int TP, int METHOD, int PREC>
-__global__ __launch_bounds__(1024) void k_step(SysConst c, SysPtrs p, int cur, int tail) {
-  extern __shared__ unsigned s_tail_lds[];
+// Waves per SIMD the step kernel is compiled for: blocks of 1024 threads need four.  The
+// staged form at one lane per particle takes five (with float32 positions): its LDS copy
+// leaves room for five blocks of 256.
+template <int TP, int PREC, bool STAGE>
+struct kStepWaves {
+  static constexpr int value = STAGE && TP == 1 && PREC == 0 ? 5 : 4;
+};
+
+template <int TP, int METHOD, int PREC, bool STAGE>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kStepWaves<TP, PREC, STAGE>::value))) void k_step(SysConst c, SysPtrs p, int cur, int tail) {
+  extern __shared__ unsigned s_tail_lds[];  // list build and tail of small systems; STAGE: the region copies
   __shared__ SharedPairs sp;
   __shared__ BlockPartial s_waves[16];
   __shared__ int s_flag[2];
@@ -2099,14 +2707,17 @@ __global__ __launch_bounds__(1024) void k_step(SysConst c, SysPtrs p, int cur, i
   // builder: the same lists as their list kernels), placing their sorted data; the
   // step then reads positions from the sorted copy, which the other workgroups may
   // not have placed yet
-  const int build = tail == 2 ? p.ctl->rebuild : 0;
+  const int build = !STAGE && tail == 2 ? p.ctl->rebuild : 0;
   // the friction of the step, read before the list build: the build's tallies are
   // atomics on the same control line from every workgroup, and a load queued behind
   // them waits several microseconds
   const double xi = c.thermostat ? p.ctl->xi : 0.0;
   if (build && threadIdx.x < kMaxPairs) s_cs2[threadIdx.x] = c.pt.cs2[threadIdx.x];
-  __syncthreads();
   const int lb = xcd_remap(blockIdx.x, gridDim.x);
+  float4 *const s_region = reinterpret_cast<float4 *>(s_tail_lds);
+  int place = -1;
+  if constexpr (STAGE) place = stage_fill<TP>(c, p, p.pos[cur], lb, s_region);
+  __syncthreads();
   // the positions of the step: the sorted copy on a build step after a sort, else in place
   const float4 *pos = p.pos[cur];
   if (build) {
@@ -2155,8 +2766,11 @@ __global__ __launch_bounds__(1024) void k_step(SysConst c, SysPtrs p, int cur, i
       }
     }
   }
-  force_lane<TP, METHOD, StepBatch<TP>::value>(ic, t, active, pi, pos, (const int *)p.nbl, (const int *)p.nnb, sp, c,
-                                               fx, fy, fz, u, w);
+  if (STAGE && place >= 0)
+    force_lane_staged<TP, METHOD>(ic, t, active, pi, s_region + place, p, sp, c, fx, fy, fz, u, w);
+  else
+    force_lane<TP, METHOD, StepBatch<TP>::value, STAGE>(ic, t, active, pi, pos, (const int *)p.nbl, (const int *)p.nnb, sp,
+                                                        c, fx, fy, fz, u, w);
   fx = lane_sum<TP>(fx);
   fy = lane_sum<TP>(fy);
   fz = lane_sum<TP>(fz);
@@ -2518,7 +3132,7 @@ __global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(k
         const bool by_cell = 4 * J.g * kBatchWaves <= c.ncell;
         int *wcnt = reinterpret_cast<int *>(cand + kCellWindow);
         auto direct = [&](int i, int kk, int jj) {
-          if (kk < c.n_max) p.nbl[nbl_addr(i, kk, c.tp, c.nvp)] = jj;
+          if (kk < c.n_max) p.nbl[nbl_addr(i, kk, c)] = jj;
         };
         for (int t = J.w * kBatchWaves + wv; !by_cell && t < c.n; t += J.g * kBatchWaves) {
           const int kt = list_wave_one<false>(c, p, cur, t, cand, s_cs2, tpos, cstart, longest);
@@ -2536,7 +3150,8 @@ __global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(k
             continue;
           }
           for (int l = lane; l < ne; l += 64) wcnt[l] = 0;
-          const int cx = cell % c.nc[0], cy = (cell / c.nc[0]) % c.nc[1], cz = cell / (c.nc[0] * c.nc[1]);
+          int cx, cy, cz;
+          cell_coords(tpos[e0], c, cx, cy, cz);
           list_cell_particles(c, p, cx, cy, cz, (int)e0, (int)e1, cand, wcnt, s_cs2, tpos, cstart, direct);
           for (int l = lane; l < ne; l += 64) {
             const int cn = wcnt[l];
@@ -2584,7 +3199,7 @@ __global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(k
             l0 = gload(p.last, i);
           }
         }
-        force_lane<TP, METHOD, Batch<TP>::value>(ic, t, active, pi, spos, nblg, nnbg, sp, c, fx, fy, fz, uu, w);
+        force_lane<TP, METHOD, Batch<TP>::value, false>(ic, t, active, pi, spos, nblg, nnbg, sp, c, fx, fy, fz, uu, w);
         fx = lane_sum<TP>(fx);
         fy = lane_sum<TP>(fy);
         fz = lane_sum<TP>(fz);
@@ -2891,13 +3506,36 @@ static __global__ __launch_bounds__(256) void k_direct_out(SysConst c, SysPtrs p
 
 // ---------------------------------------------------------------- launchers
 
+// Threads per particle for which the staged kernels exist.
+constexpr bool staged_tp(int tp) { return tp <= 4; }
+
+// Dynamic LDS of a step or force workgroup that copies its regions.
+inline size_t stage_lds_bytes(const SysConst &c) { return sizeof(float4) * (size_t)c.stage_lds; }
+
+// Allow a staged kernel the LDS it needs (raised once per size; a host call, not a
+// stream operation, so it may run during a capture).
+template <class F>
+hipError_t allow_lds(F *fn, size_t bytes) {
+  if (bytes <= 65536) return hipSuccess;
+  return hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+
 template <int TP>
 hipError_t launch_step_tp(int method, int prec, dim3 g, dim3 b, hipStream_t st, const SysConst &c,
                                  const SysPtrs &p, int cur, int tail, size_t lds) {
-#define SRMD_STEP_CASE(M, P)                                                   \
-  if (method == M && prec == P) {                                              \
-    hipLaunchKernelGGL((k_step<TP, M, P>), g, b, lds, st, c, p, cur, tail);    \
-    return hipGetLastError();                                                  \
+#define SRMD_STEP_CASE(M, P)                                                                 \
+  if (method == M && prec == P) {                                                            \
+    if constexpr (staged_tp(TP)) {                                                           \
+      if (c.stage) {                                                                         \
+        const size_t region = stage_lds_bytes(c);                                            \
+        const hipError_t e = allow_lds(k_step<TP, M, P, true>, region);                      \
+        if (e != hipSuccess) return e;                                                       \
+        hipLaunchKernelGGL((k_step<TP, M, P, true>), g, b, region, st, c, p, cur, tail);     \
+        return hipGetLastError();                                                            \
+      }                                                                                      \
+    }                                                                                        \
+    hipLaunchKernelGGL((k_step<TP, M, P, false>), g, b, lds, st, c, p, cur, tail);           \
+    return hipGetLastError();                                                                \
   }
   SRMD_STEP_CASE(0, 0) SRMD_STEP_CASE(0, 1) SRMD_STEP_CASE(0, 2)
   SRMD_STEP_CASE(1, 0) SRMD_STEP_CASE(1, 1) SRMD_STEP_CASE(1, 2)
@@ -2909,17 +3547,32 @@ hipError_t launch_step_tp(int method, int prec, dim3 g, dim3 b, hipStream_t st, 
   return hipErrorInvalidValue;
 }
 
-template <int TP>
-hipError_t launch_force_tp(int method, dim3 g, dim3 b, hipStream_t st, const SysConst &c, const SysPtrs &p,
-                                  int cur) {
-  if (method == 0) hipLaunchKernelGGL((k_force<TP, 0>), g, b, 0, st, c, p, cur);
-  else if (method == 1) hipLaunchKernelGGL((k_force<TP, 1>), g, b, 0, st, c, p, cur);
-  else if (method == 2) hipLaunchKernelGGL((k_force<TP, 2>), g, b, 0, st, c, p, cur);
-  else if (method == 3) hipLaunchKernelGGL((k_force<TP, 3>), g, b, 0, st, c, p, cur);
-  else if (method == 4) hipLaunchKernelGGL((k_force<TP, 4>), g, b, 0, st, c, p, cur);
-  else if (method == 5) hipLaunchKernelGGL((k_force<TP, 5>), g, b, 0, st, c, p, cur);
-  else return hipErrorInvalidValue;
+template <int TP, int METHOD>
+hipError_t launch_force_of(dim3 g, dim3 b, hipStream_t st, const SysConst &c, const SysPtrs &p, int cur) {
+  if constexpr (staged_tp(TP)) {
+    if (c.stage) {
+      const size_t region = stage_lds_bytes(c);
+      const hipError_t e = allow_lds(k_force<TP, METHOD, true>, region);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL((k_force<TP, METHOD, true>), g, b, region, st, c, p, cur);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((k_force<TP, METHOD, false>), g, b, 0, st, c, p, cur);
   return hipGetLastError();
+}
+
+template <int TP>
+hipError_t launch_force_tp(int method, dim3 g, dim3 b, hipStream_t st, const SysConst &c, const SysPtrs &p, int cur) {
+  switch (method) {
+    case 0: return launch_force_of<TP, 0>(g, b, st, c, p, cur);
+    case 1: return launch_force_of<TP, 1>(g, b, st, c, p, cur);
+    case 2: return launch_force_of<TP, 2>(g, b, st, c, p, cur);
+    case 3: return launch_force_of<TP, 3>(g, b, st, c, p, cur);
+    case 4: return launch_force_of<TP, 4>(g, b, st, c, p, cur);
+    case 5: return launch_force_of<TP, 5>(g, b, st, c, p, cur);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 // The templated kernels are compiled once per threads-per-particle value in a
@@ -3019,6 +3672,19 @@ int batch_max_particles() { return kSmallN; }
 
 // Dynamic LDS of the large-system persistent kernel: the list build's candidate windows.
 size_t big_lds_bytes() { return 4 * (size_t)(kBatchWaves * kWaveCand); }
+
+int stage_units(int n) { return (n + kStageSlots - 1) / kStageSlots; }
+
+size_t stage_list_lds(const SysConst &c) { return stage_list_bytes(c); }
+
+int stage_max_cells() { return kStageCells; }
+
+bool stage_supported(int tp) { return staged_tp(tp); }
+
+hipError_t launch_stage_expand(hipStream_t st, const SysConst &c, const SysPtrs &p, bool drop) {
+  hipLaunchKernelGGL(k_stage_expand, dim3(stage_units(c.n)), dim3(kStageSlots), 0, st, c, p, drop ? 1 : 0);
+  return hipGetLastError();
+}
 
 hipError_t launch_direct_init(hipStream_t st, const SysConst &c, const SysPtrs &p, const float *xyz, const int *type,
                               int *status) {
@@ -3124,6 +3790,11 @@ hipError_t launch_rebuild(hipStream_t st, const SysConst &c, const SysPtrs &p, i
   } else if (c.list_kind == 1) {
     const int lb = (c.n + 3) / 4;
     hipLaunchKernelGGL(k_list_wave, dim3(lb), dim3(tb), 0, st, c, p, cur);
+  } else if (c.stage) {
+    const hipError_t e = allow_lds(k_list_stage, stage_list_lds(c));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_list_stage, dim3(stage_units(c.n)), dim3(kStageThreads), stage_list_lds(c), st, c, p,
+                       cur);
   } else if (c.list_kind == 2) {
     hipLaunchKernelGGL(k_list_thread, dim3(gb), dim3(tb), 0, st, c, p, cur);
   } else if (c.list_kind == 5) {

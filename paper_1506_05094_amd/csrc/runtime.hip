@@ -29,6 +29,10 @@ hipError_t launch_finish(int mode, int G, int next, hipStream_t st, const SysCon
 hipError_t launch_host_sort(hipStream_t st, const SysConst &c, const SysPtrs &p, int cur);
 hipError_t launch_call_begin(hipStream_t st, const SysConst &c, const SysPtrs &p, const Snapshot &snap, int cur,
                              int thermo_every, long long trace_cap);
+int stage_units(int n);
+int stage_max_cells();
+bool stage_supported(int tp);
+hipError_t launch_stage_expand(hipStream_t st, const SysConst &c, const SysPtrs &p, bool drop);
 hipError_t launch_state_out(hipStream_t st, const SysPtrs &p, int n, int cur, const StateXfer &o);
 hipError_t launch_state_in(hipStream_t st, const SysPtrs &p, int n, int cur, const float L[3], const StateXfer &in);
 hipError_t launch_direct_init(hipStream_t st, const SysConst &c, const SysPtrs &p, const float *xyz, const int *type,
@@ -125,6 +129,8 @@ struct srmd_system {
   int n_max = 0, nvp = 0, ncell_alloc = 0;
   long long nbl_alloc = 0;
   long long trace_alloc = 0;
+  long long list16_alloc = 0;
+  size_t stage_alloc = 0;
   int part_alloc = 0;
   std::vector<DevBuf> bufs;
   // snapshot for list-overflow replay
@@ -421,12 +427,52 @@ srmd_status fill_const(srmd_system *s) {
   c.volume = V;
   const bool fits = small_sort_fits(s->n, c.ncell);
   c.small_sort = (s->sort_mode == 0 || s->sort_mode == 1) && fits ? 1 : 0;
-  // measured on MI355X (LJ fluid): the cell builder is fastest from 16k to 64k particles and
-  // the thread builder from 256k on; the autotuner compares all three
-  c.list_kind = s->list_mode != 0 ? s->list_mode : s->n <= 4096 ? 1 : s->n <= 131072 ? 3 : 2;
+  // measured on MI355X (LJ fluid): without staged lists the cell builder is fastest from
+  // 16k to 64k particles and the thread builder from 256k on; the staged form of the
+  // thread builder (below) is the fastest wherever it applies; the autotuner compares all
+  const bool auto_cell = s->list_mode == 0 && s->n > 4096 && s->n <= 131072;
+  c.list_kind = s->list_mode != 0 ? s->list_mode : s->n <= 4096 ? 1 : c.small_sort ? 3 : 2;
   if (c.list_kind == 4 && !c.small_sort)
     return fail(s, SRMD_EINVAL, "the all-pairs list build takes systems of at most 8192 particles and 8192 cells "
                                 "with the one-workgroup sort mode");
+  // cell order: columns of tiles for large systems (the row-staged builder reads whole
+  // rows of cells as consecutive slots, so with it the order stays row-major)
+  for (int k = 0; k < 2; ++k) {
+    c.tiles[k] = c.small_sort || c.list_kind == 5 ? 1 : std::max(1, c.nc[k] / 5);
+    c.tile_q[k] = c.nc[k] / c.tiles[k];
+    c.tile_rem[k] = c.nc[k] % c.tiles[k];
+    c.tile_mq[k] = 65536 / c.tile_q[k] + 1;
+    c.tile_mq1[k] = 65536 / (c.tile_q[k] + 1) + 1;
+  }
+  while ((1 << c.tp_shift) < s->tp) ++c.tp_shift;
+  // Staged lists (k_list_stage and the staged step and force kernels): large systems
+  // with the thread-per-particle list and blocks of whole units.  What a unit copies is
+  // its slab (about 5 x 5 cells and the layers that hold its slots) widened by the list
+  // radius, and a third more (over jittered lattices of 16 000 to 256 000 particles of
+  // both fluids no unit needed more than 1.15 times the estimate, nor did those that end
+  // one column and begin the next).  10 cells along every axis, so that
+  // a test without image arithmetic never sees a distance of half a box side.
+  if (!c.small_sort && c.list_kind == 2 && stage_supported(s->tp) && s->ppb % kStageSlots == 0 && c.nc[0] >= 10 &&
+      c.nc[1] >= 10 && c.nc[2] >= 10 && s->n < (1 << 28)) {
+    const double rho = s->n / V, a = c.tile_q[0] * c.Ld[0] / c.nc[0], b = c.tile_q[1] * c.Ld[1] / c.nc[1];
+    const double layers = kStageSlots / (rho * a * b) / (c.Ld[2] / c.nc[2]);
+    const double h = (layers + 0.6) * c.Ld[2] / c.nc[2];
+    const double region = rho * (a * b * h + 2.0 * reach * (a * b + b * h + a * h) + M_PI * reach * reach * (a + b + h) +
+                                 4.0 / 3.0 * M_PI * reach * reach * reach);
+    const double cells = (c.tile_q[0] + 4.0) * (c.tile_q[1] + 4.0) * (layers + 5.0);
+    const int units = s->ppb / kStageSlots;
+    // with one unit per block, what lets five blocks share a compute unit's LDS (32 000
+    // bytes with the static 2.4 KB) if that is still a fifth more than the estimate
+    int cap = std::max(1024, (int)(1.35 * region));
+    if (s->tp == 1 && units == 1 && 1.2 * region <= 1850) cap = std::min(cap, 1850);
+    if (units * (cap + 1) <= 9400 && 1.3 * cells <= stage_max_cells()) {
+      c.stage = 1;
+      c.stage_cap = cap;
+      c.stage_lds = units * (cap + 1);
+      c.stage_reach2 = (float)(reach * reach * (1.0 + 1e-3));
+    }
+  }
+  if (auto_cell && !c.stage) c.list_kind = 3;
   c.list_blocks = std::max(1, std::min((s->n + 255) / 256, 2048));
   c.pot_kind = s->pot >= 2 ? s->pot : 0;
   c.sort_every = c.list_kind == 4 ? s->sort_every : 0;
@@ -550,6 +596,23 @@ srmd_status prepare(srmd_system *s) {
     s->p.part = (BlockPartial *)dev_alloc(s, sizeof(BlockPartial) * (size_t)nparts);
     if (!s->p.part) return fail(s, SRMD_ENOMEM, "partials allocation failed");
     s->part_alloc = nparts;
+  }
+  if (c.stage) {
+    const size_t units = (size_t)stage_units(s->n);
+    if (need_nbl / 2 > s->list16_alloc) {
+      dev_free(s, s->p.list16);
+      s->p.list16 = (unsigned *)dev_alloc(s, sizeof(unsigned) * (size_t)(need_nbl / 2));
+      s->list16_alloc = s->p.list16 ? need_nbl / 2 : 0;
+    }
+    if (units * (size_t)c.stage_cap > s->stage_alloc) {
+      dev_free(s, s->p.stage_src);
+      s->p.stage_src = (unsigned *)dev_alloc(s, sizeof(unsigned) * units * (size_t)c.stage_cap);
+      s->stage_alloc = s->p.stage_src ? units * (size_t)c.stage_cap : 0;
+    }
+    if (!s->p.stage_n) s->p.stage_n = (int *)dev_alloc(s, sizeof(int) * units);
+    if (!s->p.list16 || !s->p.stage_src || !s->p.stage_n)
+      return fail(s, SRMD_ENOMEM, "staged list allocation failed");
+    HIPCHK(s, hipMemsetAsync(s->p.stage_n, 0, sizeof(int) * units, s->stream));
   }
   resolve_persistent(s);
   drop_graphs(s);
@@ -697,6 +760,13 @@ ReplicaDesc make_desc(const srmd_system *s) {
   return d;
 }
 
+// The lists of staged units as plain entries in nbl, for the readers of nbl; drop: from
+// now on the units' lists are the plain ones.
+srmd_status plain_lists(srmd_system *s, bool drop) {
+  if (s->c.stage) HIPCHK(s, launch_stage_expand(s->stream, s->c, s->p, drop));
+  return SRMD_OK;
+}
+
 // One launch of the persistent kernel over cnt steps: the system split over
 // persist_groups workgroups (job w of g on workgroup w).
 srmd_status launch_persistent(srmd_system *s, int cnt) {
@@ -732,6 +802,9 @@ srmd_status launch_persistent(srmd_system *s, int cnt) {
     HIPCHK(s, hipStreamSynchronize(s->stream));
     s->desc_valid = true;
   }
+  // the persistent kernel reads and builds plain lists
+  srmd_status sl = plain_lists(s, true);
+  if (sl != SRMD_OK) return sl;
   if (g > 1) HIPCHK(s, hipMemsetAsync(s->p.bar_flags, 0, sizeof(unsigned) * 2 * 256, s->stream));
   HIPCHK(s, launch_multi(s->tp, kmethod(s), !s->c.small_sort, g, persist_lds(s), s->stream, s->d_desc, s->d_jobs, s->d_job_off,
                          cnt, g > 1));
@@ -1780,6 +1853,10 @@ srmd_status srmd_save_state(srmd_system *s, void *buf, size_t bytes, size_t *nee
     q += b;
     return e;
   };
+  if (rows > 0) {
+    st = plain_lists(s, false);
+    if (st != SRMD_OK) return st;
+  }
   HIPCHK(s, d2h(s->p.pos[s->cur], sizeof(float4) * n));
   HIPCHK(s, d2h(s->p.vel, sizeof(float4) * n));
   HIPCHK(s, d2h(s->p.img, sizeof(int4) * n));
@@ -1848,6 +1925,8 @@ srmd_status srmd_load_state(srmd_system *s, const void *buf, size_t bytes) {
   if (s->p.pos64) HIPCHK(s, h2d(s->p.pos64, 3 * sizeof(double) * n));
   if (s->p.kahan) HIPCHK(s, h2d(s->p.kahan, sizeof(float4) * n));
   if (keep_list) HIPCHK(s, h2d(s->p.nbl, list_b));
+  if (keep_list && s->c.stage)  // the restored lists are plain ones
+    HIPCHK(s, hipMemsetAsync(s->p.stage_n, 0, sizeof(int) * (size_t)stage_units(s->n), s->stream));
   Control c = h.ctl;
   c.error = 0;
   if (!keep_list) {
@@ -1873,6 +1952,8 @@ srmd_status srmd_get_neighbor_pairs(srmd_system *s, int32_t *pairs, int64_t cap,
   std::vector<int4> hi(n);
   std::vector<int> nn(n);
   std::vector<int> nb((size_t)s->c.n_max * (size_t)s->c.nvp);
+  const srmd_status sl = plain_lists(s, false);
+  if (sl != SRMD_OK) return sl;
   HIPCHK(s, hipMemcpyAsync(hi.data(), s->p.img, sizeof(int4) * n, hipMemcpyDeviceToHost, s->stream));
   HIPCHK(s, hipMemcpyAsync(nn.data(), s->p.nnb, sizeof(int) * n, hipMemcpyDeviceToHost, s->stream));
   HIPCHK(s, hipMemcpyAsync(nb.data(), s->p.nbl, sizeof(int) * nb.size(), hipMemcpyDeviceToHost, s->stream));

@@ -20,6 +20,8 @@ __host__ __device__ inline int scan_tile_shift(int ncell) {
 }
 __host__ __device__ inline int scan_tiles(int ncell) { return ((ncell - 1) >> scan_tile_shift(ncell)) + 1; }
 
+constexpr int kStageSlots = 256;  // sorted slots of a unit of the staged lists
+
 // Per-type-pair float32 constants of the pair kernel and of the list build.
 struct PairTable {
   float cs2[kMaxPairs];    // (rc_ab + skin)^2 rounded once to float32: list radius
@@ -73,7 +75,17 @@ struct SysConst {
   int list_blocks;   // grid of the thread-per-particle list build and the sort kernels
   int pot_kind;      // kernel method 5: 2 Yukawa, 3 Buckingham, 4 Gaussian core, 5 Dzugutov, 6 Girifalco
   int sort_every;    // all-pairs lists (list_kind 4): spatial sort at every k-th build (0: never)
-  int pad1;
+  int tp_shift;      // log2 of tp
+  // Cell order of large systems (cell_id): columns of about 5 x 5 cells along z.  Per
+  // axis x, y: the tiles, their width q (the first rem tiles are one wider) and the
+  // reciprocals ceil(2^16 / q), ceil(2^16 / (q + 1)); one tile: row-major cells.
+  int tiles[2], tile_q[2], tile_rem[2], tile_mq[2], tile_mq1[2];
+  // Staged lists (large systems): the neighbourhood of kStageSlots consecutive slots (a
+  // unit) is copied to LDS and the lists hold 16-bit places in that copy.
+  int stage;         // 1: used
+  int stage_cap;     // particles the copy of one unit's region holds at most
+  int stage_lds;     // particles the LDS of a step or force workgroup holds
+  float stage_reach2; // square of the largest list radius, with a margin
   float inv_mass[kMaxTypes];
   double mass[kMaxTypes];
   PairTable pt;
@@ -128,6 +140,9 @@ struct SysPtrs {
   float4 *kahan;    // Kahan residuals or nullptr
   int *nbl;         // neighbour list, tp-interleaved column-major
   int *nnb;         // list lengths
+  unsigned *list16; // staged lists: two 16-bit entries per word, tp-interleaved column-major
+  unsigned *stage_src; // slots of each unit's region, in the order of its copy (stage_cap per unit)
+  int *stage_n;     // particles of each unit's region; 0: the unit's lists are in nbl
   unsigned *cell_of;
   unsigned *slot_in_cell;
   unsigned *cell_count;
