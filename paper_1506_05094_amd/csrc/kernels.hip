@@ -929,6 +929,17 @@ __device__ __forceinline__ void place_sorted(const SysPtrs &p, int cur, int t, c
   }
 }
 
+// Whether a rebuild kernel has work.  cur < 0: a run-ahead chain, in which the position
+// buffer is the device's and nothing runs once the call's last step is done; the loads
+// are issued together.
+__device__ __forceinline__ bool rebuild_due(const Control *ctl, int &cur) {
+  const int flag = ctl->rebuild, buf = ctl->cur;
+  const long long step = ctl->step, stop = ctl->stop;
+  if (cur >= 0) return flag != 0;
+  cur = buf;
+  return flag != 0 && step < stop;
+}
+
 // ---------------------------------------------------------------- multi-kernel sort (large systems)
 
 __device__ __forceinline__ void begin_build(Control *ctl) {
@@ -1081,25 +1092,25 @@ __device__ void sort_gather(const SysConst &c, const SysPtrs &p, int cur, int fi
 }
 
 static __global__ __launch_bounds__(256) void k_bin(SysConst c, SysPtrs p, int cur) {
-  if (p.ctl->rebuild == 0) return;
+  if (!rebuild_due(p.ctl, cur)) return;
   sort_bin(c, p, cur, blockIdx.x * blockDim.x, gridDim.x * blockDim.x);
 }
 
 // One workgroup per tile of cells.
-static __global__ __launch_bounds__(256) void k_scan(SysConst c, SysPtrs p) {
-  if (p.ctl->rebuild == 0) return;
+static __global__ __launch_bounds__(256) void k_scan(SysConst c, SysPtrs p, int cur) {
+  if (!rebuild_due(p.ctl, cur)) return;
   __shared__ unsigned s_w[16];
   if (blockIdx.x == 0 && threadIdx.x == 0) begin_build(p.ctl);
   sort_scan_tile(c, p, blockIdx.x, s_w);
 }
 
-static __global__ __launch_bounds__(256) void k_scatter(SysConst c, SysPtrs p) {
-  if (p.ctl->rebuild == 0) return;
+static __global__ __launch_bounds__(256) void k_scatter(SysConst c, SysPtrs p, int cur) {
+  if (!rebuild_due(p.ctl, cur)) return;
   sort_scatter(c, p, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x, blockIdx.x == 0);
 }
 
 static __global__ __launch_bounds__(256) void k_gather(SysConst c, SysPtrs p, int cur) {
-  if (p.ctl->rebuild == 0) return;
+  if (!rebuild_due(p.ctl, cur)) return;
   sort_gather(c, p, cur, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
 }
 
@@ -1387,7 +1398,7 @@ __device__ int list_allpairs_one(const SysConst &c, const SysPtrs &p, int i, con
 // All-pairs lists for the launch chain, one wave per particle, four per block; the
 // particles keep their order unless a periodic re-sort ran before this build.
 static __global__ __launch_bounds__(256) void k_list_allpairs(SysConst c, SysPtrs p, int cur) {
-  if (p.ctl->rebuild == 0) return;
+  if (!rebuild_due(p.ctl, cur)) return;
   __shared__ float s_cs2[kMaxPairs];
   if (threadIdx.x < kMaxPairs) s_cs2[threadIdx.x] = c.pt.cs2[threadIdx.x];
   __syncthreads();
@@ -1408,7 +1419,7 @@ static __global__ __launch_bounds__(256) void k_list_allpairs(SysConst c, SysPtr
 
 // One wave per particle (list_wave_one), four particles per block.
 static __global__ __launch_bounds__(256) void k_list_wave(SysConst c, SysPtrs p, int cur) {
-  if (p.ctl->rebuild == 0) return;
+  if (!rebuild_due(p.ctl, cur)) return;
   __shared__ float s_cs2[kMaxPairs];
   __shared__ unsigned s_cand[4][kWaveCand];
   if (threadIdx.x < kMaxPairs) s_cs2[threadIdx.x] = c.pt.cs2[threadIdx.x];
@@ -1445,7 +1456,7 @@ __device__ __forceinline__ int wave_min_int(int v) {
 // span.  A lane that runs kRing slots ahead of the slowest lane writes its later
 // entries directly.
 static __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_list_thread(SysConst c, SysPtrs p, int cur) {
-  if (p.ctl->rebuild == 0) return;
+  if (!rebuild_due(p.ctl, cur)) return;
   __shared__ float s_cs2[kMaxPairs];
   __shared__ int s_ring[4][kRing][64];
   if (threadIdx.x < kMaxPairs) s_cs2[threadIdx.x] = c.pt.cs2[threadIdx.x];
@@ -1768,7 +1779,7 @@ __host__ __device__ inline size_t stage_list_bytes(const SysConst &c) {
 // 64 000.  A unit whose region does not fit (several columns, crowded cells) gets plain
 // lists, a wave per particle, from device memory.
 static __global__ __launch_bounds__(kStageThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_list_stage(SysConst c, SysPtrs p, int cur) {
-  if (p.ctl->rebuild == 0) return;
+  if (!rebuild_due(p.ctl, cur)) return;
   extern __shared__ float4 s_pos[];
   __shared__ float s_cs2[kMaxPairs];
   __shared__ unsigned s_w[16];
@@ -1971,7 +1982,7 @@ constexpr int kRowCap = 1024;    // particles of a stencil row staged in LDS
 constexpr int kRowCells = 1024;  // cells per x-row the cell starts of LDS hold (nc <= 1024)
 
 static __global__ __launch_bounds__(256) void k_list_row(SysConst c, SysPtrs p, int cur) {
-  if (p.ctl->rebuild == 0) return;
+  if (!rebuild_due(p.ctl, cur)) return;
   __shared__ float s_cs2[kMaxPairs];
   __shared__ int s_ring[4][kRing][64];
   __shared__ float4 s_row[kRowCap];
@@ -2122,7 +2133,7 @@ constexpr int kCellStage = 128;  // list entries per particle staged in LDS
 // by the workgroup in address order, so each entry index of the column-major list is
 // one contiguous span; entries past kCellStage are written directly.
 static __global__ __launch_bounds__(128) void k_list_cell(SysConst c, SysPtrs p, int cur) {
-  if (p.ctl->rebuild == 0) return;
+  if (!rebuild_due(p.ctl, cur)) return;
   __shared__ float s_cs2[kMaxPairs];
   __shared__ int s_list[kCellSlots][kCellStage + 1];  // +1: entries of one particle fall in distinct banks
   __shared__ unsigned s_cand[2][kCellWindow];
@@ -2668,6 +2679,7 @@ __device__ void step_tail(const SysConst &c, const SysPtrs &p, int G, int next, 
   if (threadIdx.x == 0) {
     s_flag[0] = finish_step(c, p, a, cv);
     s_flag[1] = resort_due(c, cv.n_rebuilds) ? 1 : 0;
+    p.ctl->cur = next;
   }
   __syncthreads();
   if (s_flag[0] && c.small_sort) {
@@ -2700,6 +2712,15 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kStepWaves
   __shared__ int s_flag[2];
   __shared__ float s_cs2[kMaxPairs];
   const unsigned long long tstart = wall_clock64();
+  // cur < 0: a step of a run-ahead chain; -1 follows a rebuild slot, -2 does not and
+  // waits for the next one when the flag is set.  Every workgroup reads the words before
+  // the last one, which ends the step, writes them.
+  if (cur < 0) {
+    const int flag = p.ctl->rebuild, buf = p.ctl->cur;
+    const long long now = p.ctl->step, stop = p.ctl->stop;
+    if (now >= stop || (cur == -2 && flag != 0)) return;
+    cur = buf;
+  }
   stage_pairs(sp, c);
   // tail 2: a small system's list is built here, at the start of a step whose
   // rebuild flag is set (no list kernel in the chain): each wave builds the lists of
@@ -3315,13 +3336,15 @@ const void *multi_fn(int method) {
 // last-build positions, images and ids, precision residuals and the control block
 // itself) is copied into the replay snapshot.
 static __global__ __launch_bounds__(256) void k_call_begin(SysConst c, SysPtrs p, Snapshot snap, int cur, int thermo_every,
-                                                    long long trace_cap) {
+                                                           long long trace_cap, long long nsteps) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i == 0) {
     Control k = *p.ctl;
     k.thermo_every = thermo_every;
     k.trace_cap = trace_cap;
     k.n_records = 0;
+    k.cur = cur;
+    k.stop = k.step + nsteps;
     *p.ctl = k;
     *snap.ctl = k;
   }
@@ -3337,6 +3360,12 @@ static __global__ __launch_bounds__(256) void k_call_begin(SysConst c, SysPtrs p
       snap.pos64[3 * i + 2] = p.pos64[3 * i + 2];
     }
   }
+}
+
+// The words of a run-ahead chain: the position buffer of the next step and the last step.
+static __global__ void k_arm(Control *ctl, int cur, long long nsteps) {
+  ctl->cur = cur;
+  ctl->stop = ctl->step + nsteps;
 }
 
 // ---------------------------------------------------------------- state transfers
@@ -3698,6 +3727,11 @@ hipError_t launch_direct_out(hipStream_t st, const SysConst &c, const SysPtrs &p
   return hipGetLastError();
 }
 
+hipError_t launch_arm(hipStream_t st, Control *ctl, int cur, long long nsteps) {
+  hipLaunchKernelGGL(k_arm, dim3(1), dim3(1), 0, st, ctl, cur, nsteps);
+  return hipGetLastError();
+}
+
 hipError_t launch_state_out(hipStream_t st, const SysPtrs &p, int n, int cur, const StateXfer &o) {
   hipLaunchKernelGGL(k_state_out, dim3((n + 255) / 256), dim3(256), 0, st, p, n, cur, o);
   return hipGetLastError();
@@ -3710,8 +3744,9 @@ hipError_t launch_state_in(hipStream_t st, const SysPtrs &p, int n, int cur, con
 }
 
 hipError_t launch_call_begin(hipStream_t st, const SysConst &c, const SysPtrs &p, const Snapshot &snap, int cur,
-                             int thermo_every, long long trace_cap) {
-  hipLaunchKernelGGL(k_call_begin, dim3((c.n + 255) / 256), dim3(256), 0, st, c, p, snap, cur, thermo_every, trace_cap);
+                             int thermo_every, long long trace_cap, long long nsteps) {
+  hipLaunchKernelGGL(k_call_begin, dim3((c.n + 255) / 256), dim3(256), 0, st, c, p, snap, cur, thermo_every, trace_cap,
+                     nsteps);
   return hipGetLastError();
 }
 
@@ -3780,8 +3815,8 @@ hipError_t launch_rebuild(hipStream_t st, const SysConst &c, const SysPtrs &p, i
   const int gb = c.list_blocks;
   if (!c.small_sort) {
     hipLaunchKernelGGL(k_bin, dim3(gb), dim3(tb), 0, st, c, p, cur);
-    hipLaunchKernelGGL(k_scan, dim3(scan_tiles(c.ncell)), dim3(256), 0, st, c, p);
-    hipLaunchKernelGGL(k_scatter, dim3(gb), dim3(tb), 0, st, c, p);
+    hipLaunchKernelGGL(k_scan, dim3(scan_tiles(c.ncell)), dim3(256), 0, st, c, p, cur);
+    hipLaunchKernelGGL(k_scatter, dim3(gb), dim3(tb), 0, st, c, p, cur);
     hipLaunchKernelGGL(k_gather, dim3(gb), dim3(tb), 0, st, c, p, cur);
   }
   if (c.list_kind == 4) {

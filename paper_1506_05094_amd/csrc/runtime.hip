@@ -28,11 +28,13 @@ hipError_t launch_rebuild(hipStream_t st, const SysConst &c, const SysPtrs &p, i
 hipError_t launch_finish(int mode, int G, int next, hipStream_t st, const SysConst &c, const SysPtrs &p);
 hipError_t launch_host_sort(hipStream_t st, const SysConst &c, const SysPtrs &p, int cur);
 hipError_t launch_call_begin(hipStream_t st, const SysConst &c, const SysPtrs &p, const Snapshot &snap, int cur,
-                             int thermo_every, long long trace_cap);
+                             int thermo_every, long long trace_cap,
+                             long long nsteps);
 int stage_units(int n);
 int stage_max_cells();
 bool stage_supported(int tp);
 hipError_t launch_stage_expand(hipStream_t st, const SysConst &c, const SysPtrs &p, bool drop);
+hipError_t launch_arm(hipStream_t st, Control *ctl, int cur, long long nsteps);
 hipError_t launch_state_out(hipStream_t st, const SysPtrs &p, int n, int cur, const StateXfer &o);
 hipError_t launch_state_in(hipStream_t st, const SysPtrs &p, int n, int cur, const float L[3], const StateXfer &in);
 hipError_t launch_direct_init(hipStream_t st, const SysConst &c, const SysPtrs &p, const float *xyz, const int *type,
@@ -76,6 +78,9 @@ constexpr int kBuildPerWave = 8;          // most particles a wave of the step k
 constexpr int kBuildPerWaveAllPairs = 2;  // the same with all-pairs lists (N candidates each: measured slower at 4 and 8)
 constexpr double kTunerListKeep = 1.05;   // list methods within 5 % of the fastest at the default layout go on to phase II
 constexpr int kPersistChunk = 500;  // steps per launch of the persistent kernel (even)
+constexpr int kAheadSlots[] = {8, 12, 20, 32};  // run-ahead chains: steps enqueued after a rebuild slot
+constexpr long long kAheadLinks = 256;  // most links enqueued before the host reads the progress
+constexpr int kAheadMin = 4;        // fewest remaining steps that run ahead
 
 }  // namespace
 
@@ -145,6 +150,9 @@ struct srmd_system {
   size_t h_xfer = 0;        // bytes of a state transfer that fit behind it (0: larger systems)
   char *d_xfer = nullptr;   // device copy of a state in original order (state_bytes_xfer)
   std::map<std::pair<int, int>, hipGraphExec_t> graphs;
+  int ahead_slots = kAheadSlots[0];  // run-ahead chains: steps after a rebuild slot
+  long long ahead_step = -1, ahead_builds = 0;  // steps and list builds at the last reading (-1: none yet)
+  double ahead_rate = 0;             // steps done per rebuild slot, as last measured (0: not yet)
   std::string err;
 };
 
@@ -659,6 +667,17 @@ srmd_status enqueue_steps(srmd_system *s, int count, int cur) {
   return SRMD_OK;
 }
 
+// One link of a run-ahead chain: a rebuild slot and the steps after it (see run_ahead).
+srmd_status enqueue_ahead(srmd_system *s, int slots) {
+  HIPCHK(s, launch_rebuild(s->stream, s->c, s->p, -1));
+  for (int k = 0; k < slots; ++k)
+    HIPCHK(s, launch_step(s->tp, kmethod(s), (int)s->prec, step_blocks(s), s->tp * s->ppb, s->stream, s->c, s->p,
+                          k == 0 ? -1 : -2, 1, tail_lds_bytes(s->c, s->tp * s->ppb, 1)));
+  return SRMD_OK;
+}
+
+// The captured graph of count steps from position buffer cur (count < 0: a run-ahead
+// link of -count steps).
 srmd_status get_graph(srmd_system *s, int count, int cur, hipGraphExec_t *out) {
   auto key = std::make_pair(count, cur);
   auto it = s->graphs.find(key);
@@ -668,7 +687,7 @@ srmd_status get_graph(srmd_system *s, int count, int cur, hipGraphExec_t *out) {
   }
   hipGraph_t g;
   HIPCHK(s, hipStreamBeginCapture(s->stream, hipStreamCaptureModeThreadLocal));
-  srmd_status st = enqueue_steps(s, count, cur);
+  srmd_status st = count > 0 ? enqueue_steps(s, count, cur) : enqueue_ahead(s, -count);
   hipGraph_t g2 = nullptr;
   hipError_t e = hipStreamEndCapture(s->stream, &g2);
   if (st != SRMD_OK) {
@@ -825,12 +844,66 @@ srmd_status run_persistent(srmd_system *s, long long nsteps) {
   return SRMD_OK;
 }
 
-srmd_status run_steps(srmd_system *s, long long nsteps) {
+// Large systems: a rebuild is five kernels, which cost about 1.5 us each in every step
+// that does not need them (7.5 of 29 us at 16 000 particles).  A run-ahead link has one
+// rebuild slot and then several steps; a step finds the flag set and exits (1.5 us) until
+// the next slot, and all exit once the call's last step is done.  Links are enqueued for
+// the steps left at the rate that the list lasts, the host then reads how far the device
+// came and enqueues what is missing.  The slots after a rebuild follow the mean list
+// lifetime I (8 up to I = 8.5, then 12, 20, 32): fewer leave rebuild slots idle, more
+// leave steps idle.  *left: the steps not done; on return fewer than kAheadMin, or the
+// list overflowed (h->ctl is the control block as read last).
+srmd_status run_ahead(srmd_system *s, long long *left) {
+  while (*left >= kAheadMin) {
+    const int slots = s->ahead_slots;
+    const double rate = s->ahead_rate > 0 ? std::min((double)slots, s->ahead_rate) : (double)slots;
+    const long long links = std::min(kAheadLinks, std::max(1LL, (long long)std::ceil((double)*left / rate)));
+    hipGraphExec_t ge;
+    srmd_status st = get_graph(s, -slots, 0, &ge);
+    if (st != SRMD_OK) return st;
+    for (long long k = 0; k < links; ++k) HIPCHK(s, hipGraphLaunch(ge, s->stream));
+    st = read_ctl(s, &s->h->ctl);
+    if (st != SRMD_OK) return st;
+    const Control &h = s->h->ctl;
+    const long long rest = h.stop - h.step, done = *left - rest;
+    if (rest < 0 || done <= 0) return fail(s, SRMD_EHIP, "run-ahead chain made no progress");
+    s->cur ^= (int)(done & 1);
+    *left = rest;
+    // mean list lifetime since the last reading (other calls may lie between)
+    const long long steps = h.step - s->ahead_step, builds = h.n_rebuilds - s->ahead_builds;
+    const bool known = s->ahead_step >= 0 && steps >= 16 && builds >= 0;
+    s->ahead_step = h.step;
+    s->ahead_builds = h.n_rebuilds;
+    if (known) {
+      const double life = (double)steps / (double)std::max(1LL, builds);
+      s->ahead_slots = life <= 8.5 ? kAheadSlots[0] : life <= 12.5 ? kAheadSlots[1] : life <= 20.5 ? kAheadSlots[2] : kAheadSlots[3];
+      s->ahead_rate = life / std::ceil(life / s->ahead_slots);
+      st = get_graph(s, -s->ahead_slots, 0, &ge);  // captured now rather than in the next round
+      if (st != SRMD_OK) return st;
+    }
+    if (h.error & 2) return SRMD_OK;
+  }
+  return SRMD_OK;
+}
+
+// nsteps steps; armed: the control block holds the call's position buffer and last step
+// (k_call_begin).  *synced: the control block has been read back after the last step.
+srmd_status run_steps(srmd_system *s, long long nsteps, bool armed = false, bool *synced = nullptr) {
+  if (synced) *synced = false;
   srmd_status st0 = flush_host_sort(s);
   if (st0 != SRMD_OK) return st0;
   if (!s->persist_err.empty()) return fail(s, SRMD_EUNSUPPORTED, s->persist_err);
   if (s->persist_groups > 0) return run_persistent(s, nsteps);
   long long left = nsteps;
+  if (!s->c.small_sort && step_tail(s) == 1 && left >= kAheadMin) {
+    if (!armed) HIPCHK(s, launch_arm(s->stream, s->p.ctl, s->cur, nsteps));
+    st0 = run_ahead(s, &left);
+    if (st0 != SRMD_OK) return st0;
+    if (left == 0 || (s->h->ctl.error & 2)) {
+      if (synced) *synced = true;
+      return SRMD_OK;
+    }
+  }
   while (left > 0) {
     const int cnt = (int)std::min<long long>(left, kChunk);
     hipGraphExec_t ge;
@@ -1216,12 +1289,15 @@ srmd_status restore_and_regrow(srmd_system *s, int cur0) {
 srmd_status run_with_replay(srmd_system *s, long long nsteps, int32_t thermo_every, long long cap) {
   for (int attempt = 0; attempt < 8; ++attempt) {
     const int cur0 = s->cur;
-    HIPCHK(s, launch_call_begin(s->stream, s->c, s->p, s->snap, s->cur, thermo_every, cap));
-    srmd_status st = run_steps(s, nsteps);
+    HIPCHK(s, launch_call_begin(s->stream, s->c, s->p, s->snap, s->cur, thermo_every, cap, nsteps));
+    bool synced = false;
+    srmd_status st = run_steps(s, nsteps, true, &synced);
     if (st != SRMD_OK) return st;
-    // the one host round trip of the call: the control block's sticky error word
-    HIPCHK(s, hipMemcpyAsync(&s->h->ctl, s->p.ctl, sizeof(Control), hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(s, hipStreamSynchronize(s->stream));
+    // the host round trip of the call: the control block's sticky error word
+    if (!synced) {
+      st = read_ctl(s, &s->h->ctl);
+      if (st != SRMD_OK) return st;
+    }
     Control h = s->h->ctl;
     st = check_barrier(s, &h);
     if (st != SRMD_OK) return st;
@@ -2953,7 +3029,7 @@ srmd_status srmd_batch_step(srmd_batch *b, int64_t nsteps, int32_t thermo_every,
   for (auto *s : b->sys) {
     // trace settings and replay snapshot in one launch, then a host-requested
     // rebuild's spatial sort, both on the system's stream before the batched launch
-    if (launch_call_begin(s->stream, s->c, s->p, s->snap, s->cur, thermo_every, cap) != hipSuccess)
+    if (launch_call_begin(s->stream, s->c, s->p, s->snap, s->cur, thermo_every, cap, nsteps) != hipSuccess)
       return bfail(b, SRMD_EHIP, "replica call start failed");
     st = flush_host_sort(s);
     if (st != SRMD_OK) return bfail(b, st, s->err);

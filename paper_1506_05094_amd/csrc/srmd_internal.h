@@ -108,7 +108,9 @@ struct Control {
   unsigned long long prof_ticks;  // accumulated step-kernel durations (device clock ticks)
   long long prof_count;           // step kernels accumulated
   int resorted;                   // all-pairs lists: the build ahead starts from a fresh spatial sort
-  int pad[41];
+  int cur;                        // position buffer of the next step
+  long long stop;                 // run-ahead chains: no step beyond this step count
+  int pad[38];
 };
 
 static_assert(sizeof(Control) == 256, "control block layout");
