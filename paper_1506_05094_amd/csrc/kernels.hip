@@ -2124,19 +2124,25 @@ __device__ void list_cell_particles(const SysConst &c, const SysPtrs &p, int cx,
 }
 
 constexpr int kCellSlots = 32;   // sorted slots per workgroup of the cell builder
+constexpr int kCellWaves = 8;    // its waves
+constexpr int kCellPiece = 4;    // particles of a cell one wave takes at most
 constexpr int kCellStage = 128;  // list entries per particle staged in LDS
 
 // Verlet lists, one wave per cell (list_cell_particles), for the launch chain.  A
-// workgroup of two waves takes kCellSlots consecutive sorted slots, split into runs
-// of one cell (a cell that straddles two workgroups is handled by both, each for its
-// own slots).  The lists are staged in LDS as [particle][entry] and then written out
+// workgroup takes kCellSlots consecutive sorted slots, split into pieces of at most
+// kCellPiece slots of one cell (a cell that straddles two workgroups is handled by both,
+// each for its own slots), dealt over its waves.  Bound by the latency of a piece (its
+// candidates' indices, then positions, then the tests), so the pieces are many and the
+// waves eight: with two waves and whole cells a wave took about seven cells of a liquid
+// one after the other (54 -> 27 us a build for the liquid of 16 000, 178 -> 115 for the
+// salt of 20 000, 50 -> 26 for the mixture of 5003).  The lists are staged in LDS as [particle][entry] and then written out
 // by the workgroup in address order, so each entry index of the column-major list is
 // one contiguous span; entries past kCellStage are written directly.
-static __global__ __launch_bounds__(128) void k_list_cell(SysConst c, SysPtrs p, int cur) {
+static __global__ __launch_bounds__(64 * kCellWaves) void k_list_cell(SysConst c, SysPtrs p, int cur) {
   if (!rebuild_due(p.ctl, cur)) return;
   __shared__ float s_cs2[kMaxPairs];
   __shared__ int s_list[kCellSlots][kCellStage + 1];  // +1: entries of one particle fall in distinct banks
-  __shared__ unsigned s_cand[2][kCellWindow];
+  __shared__ unsigned s_cand[kCellWaves][kCellWindow];
   __shared__ int s_cnt[kCellSlots];
   __shared__ int s_seg[kCellSlots + 1];
   __shared__ int s_nseg;
@@ -2146,7 +2152,7 @@ static __global__ __launch_bounds__(128) void k_list_cell(SysConst c, SysPtrs p,
   const int nmax = c.n_max;
   if (tid < kMaxPairs) s_cs2[tid] = c.pt.cs2[tid];
   if (wv == 0) {
-    // runs of slots in one cell: a segment starts where the cell index changes
+    // pieces: one starts where the cell index changes and after every kCellPiece slots
     int cell = -1;
     if (lane < m) {
       const float4 r = p.t_pos[T0 + lane];
@@ -2157,7 +2163,10 @@ static __global__ __launch_bounds__(128) void k_list_cell(SysConst c, SysPtrs p,
       s_cnt[lane] = 0;
     }
     const int prev = __shfl_up(cell, 1, 64);
-    const bool head = lane < m && (lane == 0 || prev != cell);
+    const unsigned long long first = __ballot(lane < m && (lane == 0 || prev != cell));
+    // slots since the first one of the cell
+    const int since = lane - (63 - __builtin_clzll((first & ((2ull << lane) - 1ull)) | 1ull));
+    const bool head = lane < m && since % kCellPiece == 0;
     const unsigned long long hm = __ballot(head);
     if (head) s_seg[__popcll(hm & ((1ull << lane) - 1ull))] = lane;
     if (lane == 0) {
@@ -2173,7 +2182,7 @@ static __global__ __launch_bounds__(128) void k_list_cell(SysConst c, SysPtrs p,
     else if (k < nmax)
       p.nbl[nbl_addr(i, k, c)] = j;
   };
-  for (int sg = wv; sg < nseg; sg += 2) {
+  for (int sg = wv; sg < nseg; sg += kCellWaves) {
     const int l0 = s_seg[sg], l1 = s_seg[sg + 1];
     int cx, cy, cz;
     cell_coords(p.t_pos[T0 + l0], c, cx, cy, cz);
@@ -3836,7 +3845,7 @@ hipError_t launch_rebuild(hipStream_t st, const SysConst &c, const SysPtrs &p, i
     hipLaunchKernelGGL(k_list_row, dim3(c.nc[1] * c.nc[2]), dim3(256), 0, st, c, p, cur);
   } else {
     const int lb = (c.n + kCellSlots - 1) / kCellSlots;
-    hipLaunchKernelGGL(k_list_cell, dim3(lb), dim3(128), 0, st, c, p, cur);
+    hipLaunchKernelGGL(k_list_cell, dim3(lb), dim3(64 * kCellWaves), 0, st, c, p, cur);
   }
   return hipGetLastError();
 }
