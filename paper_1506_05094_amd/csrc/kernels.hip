@@ -1255,26 +1255,46 @@ constexpr int kListChunks = 4;   // 64-candidate chunks whose loads are in fligh
 // in the concatenated candidate sequence and the sequence length total.
 __device__ __forceinline__ void stencil_runs(const SysConst &c, int cx, int cy, int cz, const unsigned *cstart,
                                              unsigned &run_start, unsigned &run_len, unsigned &excl,
-                                             unsigned &total) {
+                                             unsigned &total, unsigned &over) {
   const int lane = threadIdx.x & 63;
-  const int ny = c.nc[1], nz = c.nc[2];
-  const bool fy = c.full_axis & 2, fz = c.full_axis & 4;
-  const int ny_eff = fy ? ny : 5, nz_eff = fz ? nz : 5;
+  const int nx = c.nc[0], ny = c.nc[1], nz = c.nc[2];
   int a0, a1, b0, b1;
   row_runs(c, cx, a0, a1, b0, b1);
   run_start = 0;
   run_len = 0;
+  over = 0;
   const int row = lane >> 1;
-  if (row < ny_eff * nz_eff) {
+  int yy, zz, rows = 25;
+  if (c.full_axis & 6) {
+    const bool fy = c.full_axis & 2, fz = c.full_axis & 4;
+    const int ny_eff = fy ? ny : 5, nz_eff = fz ? nz : 5;
+    rows = ny_eff * nz_eff;
     const int oy = row % ny_eff, oz = row / ny_eff;
-    const int yy = fy ? oy : (cy + oy - 2 + ny) % ny;
-    const int zz = fz ? oz : (cz + oz - 2 + nz) % nz;
-    const int x0 = (lane & 1) ? b0 : a0, x1 = (lane & 1) ? b1 : a1;
+    yy = fy ? oy : (cy + oy - 2 + ny) % ny;
+    zz = fz ? oz : (cz + oz - 2 + nz) % nz;
+  } else {
+    const int oz = row / 5;
+    yy = cy + row - 5 * oz - 2;
+    zz = cz + oz - 2;
+    const int ky = yy < 0 ? ny : yy >= ny ? -ny : 0, kz = zz < 0 ? nz : zz >= nz ? -nz : 0;
+    yy += ky;
+    zz += kz;
+    over = (ky != 0 ? 2u : 0u) | (kz != 0 ? 4u : 0u);
+  }
+  if (row < rows) {
+    const bool second = lane & 1, one = b1 < b0;
+    const int x0 = second && !one ? b0 : a0, x1 = second && !one ? b1 : a1;
+    if (cx < 2 ? !second : cx >= nx - 2 && second) over |= 1u;
     if (x1 >= x0) {
       const int first = cell_id(c, x0, yy, zz);
       // clamped to [0, n]: a run never reaches outside the sorted arrays
-      const unsigned s1 = min(cstart[first + (x1 - x0) + 1], (unsigned)c.n);
-      const unsigned s0 = min(cstart[first], s1);
+      unsigned s1 = min(cstart[first + (x1 - x0) + 1], (unsigned)c.n);
+      unsigned s0 = min(cstart[first], s1);
+      if (one) {  // half of the row's one run each
+        const unsigned mid = s0 + (s1 - s0 + 1) / 2;
+        s0 = second ? mid : s0;
+        s1 = second ? s1 : mid;
+      }
       run_start = s0;
       run_len = s1 - s0;
     }
@@ -1306,8 +1326,8 @@ __device__ int list_wave_one(const SysConst &c, const SysPtrs &p, int cur, int t
   const int ti = ptype(r);
   int cx, cy, cz;
   cell_coords(r, c, cx, cy, cz);
-  unsigned run_start, run_len, excl, total;
-  stencil_runs(c, cx, cy, cz, cstart, run_start, run_len, excl, total);
+  unsigned run_start, run_len, excl, total, over;
+  stencil_runs(c, cx, cy, cz, cstart, run_start, run_len, excl, total, over);
   const int nmax = c.n_max;
   int count = 0;
   for (unsigned wbase = 0; wbase < total; wbase += kWaveCand) {
@@ -2074,49 +2094,110 @@ constexpr int kCellWindow = 64 * kCellChunks;
 // them; a ballot compacts the hits in candidate order, so the lists equal those of
 // the particle-by-particle builders entry for entry.  cand: kCellWindow entries of
 // the wave's LDS; cnt[l]: entries found so far for particle i0 + l (LDS, the caller
-// clears it); sink(i, k, j) stores entry k of particle i (called by the hit lanes).
-template <class Sink>
-__device__ void list_cell_particles(const SysConst &c, const SysPtrs &p, int cx, int cy, int cz, int i0, int i1,
-                                    unsigned *cand, int *cnt, const float *s_cs2, const float4 *tpos,
+// clears it); sink(i, k, upto, j) stores entry k of particle i (called by the hit lanes;
+// upto: entries found so far with those of this chunk, uniform).
+
+// Lanes before this one whose bit of mask is set, plus base.
+__device__ __forceinline__ int rank_below(unsigned long long mask, int base) {
+  return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
+                                        __builtin_amdgcn_mbcnt_lo((unsigned)mask, (unsigned)base));
+}
+
+__device__ __forceinline__ float4 uniform4(const float4 v) {
+  auto first = [](float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); };
+  return make_float4(first(v.x), first(v.y), first(v.z), first(v.w));
+}
+
+// The particles [i0, i1) of a cell against one window of candidates u at q (places past
+// its end hold a candidate at infinity).  PAIR: image arithmetic per pair; otherwise (at
+// most two types) the image of a candidate relative to the cell is in its shift h.
+template <bool PAIR, class Sink>
+__device__ __forceinline__ void cell_tests(const SysConst &c, int i0, int i1, unsigned wlen,
+                                           const unsigned (&u)[kCellChunks], const float4 (&q)[kCellChunks],
+                                           const float (&h)[kCellChunks][3], int *cnt, const float *s_cs2,
+                                           const float4 *tpos, Sink sink) {
+  const int lane = threadIdx.x & 63, nt = c.ntypes;
+  for (int i = i0; i < i1; ++i) {
+    const float4 pi = uniform4(tpos[i]);
+    const float *row = s_cs2 + ptype(pi) * nt;
+    const float r0 = row[0], r1 = row[nt > 1 ? 1 : 0];
+    int count = __builtin_amdgcn_readfirstlane(cnt[i - i0]);
+#pragma unroll
+    for (int cb = 0; cb < kCellChunks; ++cb) {
+      if (64u * cb < wlen) {  // uniform over the wave
+        float r2;
+        if constexpr (PAIR) {
+          float dx, dy, dz;
+          r2 = dist2(pi, q[cb], c, dx, dy, dz);
+        } else {
+          const float dx = q[cb].x - pi.x - h[cb][0], dy = q[cb].y - pi.y - h[cb][1], dz = q[cb].z - pi.z - h[cb][2];
+          r2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
+        }
+        float lim;
+        if constexpr (PAIR)
+          lim = row[ptype(q[cb])];
+        else
+          lim = ptype(q[cb]) ? r1 : r0;
+        const bool hit = (r2 < lim) & ((int)u[cb] != i);
+        const unsigned long long mask = __ballot(hit);
+        const int upto = count + __popcll(mask);
+        if (hit) sink(i, rank_below(mask, count), upto, (int)u[cb]);
+        count = upto;
+      }
+    }
+    if (lane == 0) cnt[i - i0] = count;
+  }
+}
+
+template <class Cand, class Sink>
+__device__ __forceinline__ void list_cell_particles(const SysConst &c, const SysPtrs &p, int cx, int cy, int cz, int i0, int i1,
+                                    Cand *cand, int *cnt, const float *s_cs2, const float4 *tpos,
                                     const unsigned *cstart, Sink sink) {
+  cx = __builtin_amdgcn_readfirstlane(cx);
+  cy = __builtin_amdgcn_readfirstlane(cy);
+  cz = __builtin_amdgcn_readfirstlane(cz);
+  i0 = __builtin_amdgcn_readfirstlane(i0);
+  i1 = __builtin_amdgcn_readfirstlane(i1);
+  constexpr int kOver = 8 * (int)sizeof(Cand) - 3;  // the three wrap bits above a slot
   const int lane = threadIdx.x & 63;
-  unsigned run_start, run_len, excl, total;
-  stencil_runs(c, cx, cy, cz, cstart, run_start, run_len, excl, total);
+  const int nx = c.nc[0], ny = c.nc[1], nz = c.nc[2];
+  unsigned run_start, run_len, excl, total, over;
+  stencil_runs(c, cx, cy, cz, cstart, run_start, run_len, excl, total, over);
+  // From 7 cells per axis the cells tell the image: a candidate reached without wrapping
+  // round the box is nearer than 3 cells per axis, less than half a side, one reached by
+  // wrapping 4 or more away, so rounding the difference gives this very image, and a
+  // subtraction in its place the same bits.
+  const bool geo = min(nx, min(ny, nz)) >= 7 && c.ntypes <= 2;
+  const float sx = cx < 2 ? c.L[0] : -c.L[0], sy = cy < 2 ? c.L[1] : -c.L[1], sz = cz < 2 ? c.L[2] : -c.L[2];
+  const unsigned tag = over << kOver;
   for (unsigned wbase = 0; wbase < total; wbase += kCellWindow) {
     const unsigned wend = min(total, wbase + (unsigned)kCellWindow), wlen = wend - wbase;
     const unsigned q0 = max(excl, wbase), q1 = min(excl + run_len, wend);
-    for (unsigned q = q0; q < q1; ++q) cand[q - wbase] = run_start + (q - excl);
+    for (unsigned q = q0; q < q1; ++q) cand[q - wbase] = (Cand)(run_start + (q - excl) + tag);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     unsigned u[kCellChunks];
     float4 q[kCellChunks];
+    float h[kCellChunks][3];
 #pragma unroll
     for (int cb = 0; cb < kCellChunks; ++cb) {
       const unsigned qi = 64u * cb + (unsigned)lane;
-      u[cb] = qi < wlen ? cand[qi] : (unsigned)i0;
-      if (64u * cb < wlen) q[cb] = tpos[u[cb]];
-    }
-    for (int i = i0; i < i1; ++i) {
-      const float4 pi = tpos[i];
-      const int ti = ptype(pi);
-      int count = cnt[i - i0];
-#pragma unroll
-      for (int cb = 0; cb < kCellChunks; ++cb) {
-        if (64u * cb < wlen) {  // uniform over the wave
-          bool hit = false;
-          if (64u * cb + (unsigned)lane < wlen && (int)u[cb] != i) {
-            float dx, dy, dz;
-            const float r2 = dist2(pi, q[cb], c, dx, dy, dz);
-            hit = r2 < s_cs2[ti * c.ntypes + ptype(q[cb])];
-          }
-          const unsigned long long mask = __ballot(hit);
-          if (hit) sink(i, count + __popcll(mask & ((1ull << lane) - 1ull)), (int)u[cb]);
-          count += __popcll(mask);
-        }
+      u[cb] = qi < wlen ? (unsigned)cand[qi] : (unsigned)i0;
+      if (64u * cb < wlen) {
+        const unsigned w = u[cb] >> kOver;
+        u[cb] &= (1u << kOver) - 1u;
+        q[cb] = tpos[u[cb]];
+        h[cb][0] = w & 1u ? sx : 0.f;
+        h[cb][1] = w & 2u ? sy : 0.f;
+        h[cb][2] = w & 4u ? sz : 0.f;
+        if (qi >= wlen) q[cb].x = __builtin_inff();
       }
-      if (lane == 0) cnt[i - i0] = count;
     }
+    if (geo)
+      cell_tests<false>(c, i0, i1, wlen, u, q, h, cnt, s_cs2, tpos, sink);
+    else
+      cell_tests<true>(c, i0, i1, wlen, u, q, h, cnt, s_cs2, tpos, sink);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -2135,10 +2216,11 @@ constexpr int kCellStage = 128;  // list entries per particle staged in LDS
 // candidates' indices, then positions, then the tests), so the pieces are many and the
 // waves eight: with two waves and whole cells a wave took about seven cells of a liquid
 // one after the other (54 -> 27 us a build for the liquid of 16 000, 178 -> 115 for the
-// salt of 20 000, 50 -> 26 for the mixture of 5003).  The lists are staged in LDS as [particle][entry] and then written out
-// by the workgroup in address order, so each entry index of the column-major list is
-// one contiguous span; entries past kCellStage are written directly.
-static __global__ __launch_bounds__(64 * kCellWaves) void k_list_cell(SysConst c, SysPtrs p, int cur) {
+// salt of 20 000, 50 -> 26 for the mixture of 5003).  The lists are staged in LDS as
+// [particle][entry] and then written out by the workgroup in address order, so each
+// entry index of the column-major list is one contiguous span; entries past kCellStage
+// are written directly.
+static __global__ __launch_bounds__(64 * kCellWaves, 4) void k_list_cell(SysConst c, SysPtrs p, int cur) {
   if (!rebuild_due(p.ctl, cur)) return;
   __shared__ float s_cs2[kMaxPairs];
   __shared__ int s_list[kCellSlots][kCellStage + 1];  // +1: entries of one particle fall in distinct banks
@@ -2176,8 +2258,10 @@ static __global__ __launch_bounds__(64 * kCellWaves) void k_list_cell(SysConst c
   }
   __syncthreads();
   const int nseg = s_nseg;
-  auto stage = [&](int i, int k, int j) {
-    if (k < kCellStage)
+  auto stage = [&](int i, int k, int upto, int j) {
+    if (upto <= kCellStage)
+      s_list[i - T0][k] = j;
+    else if (k < kCellStage)
       s_list[i - T0][k] = j;
     else if (k < nmax)
       p.nbl[nbl_addr(i, k, c)] = j;
@@ -2933,8 +3017,16 @@ __device__ __forceinline__ int4 gload(const int4 *q, int i) {
 
 __device__ __forceinline__ int gload(const int *q, int i) { return ((const SRMD_GLOBAL int *)q)[i]; }
 
-constexpr int kBatchThreads = 512;  // threads of a persistent workgroup
-constexpr int kBatchWaves = kBatchThreads / 64;
+// Threads of a persistent workgroup: 512 for one system, whose steps wait for the
+// barrier between many small pieces, and 1024 for a batch at up to 8 threads per
+// particle, where a workgroup has thousands of particles to itself and the positions in
+// LDS allow one workgroup per compute unit: 256 replicas of the mixture (500 to 8000
+// particles, tp = 1) step in 470 us with 16 waves against 620 with 8.  From 16 threads per
+// particle a step is 16 times as many waves' work and the 512-thread kernel, which keeps
+// more entries in flight, stays.
+constexpr int kPersistThreads = 512;
+constexpr int kBatchThreads = 1024;
+constexpr int kBatchMaxTp = 8;
 constexpr int kCoopMaxGroups = 256;  // workgroups of one system (arrival words per parity)
 constexpr int kMaxJobs = 64;         // jobs of one workgroup
 constexpr int kLdsUnits = 64;        // wave partials of one piece kept in LDS (else in memory)
@@ -3006,16 +3098,132 @@ __device__ __forceinline__ bool coop_barrier(unsigned *flags, unsigned G, unsign
 }
 
 // Positions of all n particles into LDS, eight loads in flight per thread.
+template <int NT>
 __device__ __forceinline__ void fill_positions(float4 *dst, const float4 *src, int n) {
-  for (int base = 0; base < n; base += 8 * kBatchThreads) {
+  for (int base = 0; base < n; base += 8 * NT) {
     float4 v[8];
 #pragma unroll
-    for (int m = 0; m < 8; ++m) v[m] = gload(src, min(base + m * kBatchThreads + (int)threadIdx.x, n - 1));
+    for (int m = 0; m < 8; ++m) v[m] = gload(src, min(base + m * NT + (int)threadIdx.x, n - 1));
 #pragma unroll
     for (int m = 0; m < 8; ++m) {
-      const int k = base + m * kBatchThreads + (int)threadIdx.x;
+      const int k = base + m * NT + (int)threadIdx.x;
       if (k < n) dst[k] = v[m];
     }
+  }
+}
+
+// Cell lists of a batch: slots of one round of a workgroup, list entries per particle
+// staged in LDS (as 16-bit slots; rows of an odd number of words, so that the write-out
+// reads distinct banks), and the LDS of the stage and the waves' candidate windows.
+constexpr int kRoundSlots = 128;
+constexpr int kRoundRow = kCellStage + 2;
+constexpr int round_list_bytes(int threads) {
+  return 2 * (kRoundSlots * kRoundRow + threads / 64 * kCellWindow);
+}
+
+// Verlet lists of a batched replica by cells, for the slots of this piece (w of g).  A
+// round takes kRoundSlots consecutive sorted slots, cut into pieces of at most kCellPiece
+// slots of one cell that are dealt over the waves (list_cell_particles), stages their
+// entries in LDS and writes them out in address order.  Pieces are taken from a counter, so
+// that waves with emptier cells take more of them.  Bound by the instructions of a piece
+// (about 750 per wave); a build of 5300 particles of the mixture takes 0.95 ms on one
+// compute unit, 1.35 with a wave per cell whose lanes wrote each entry to memory by
+// themselves and read the constants through the descriptor.
+// stage: round_list_bytes(NT) bytes.  Returns this thread's entries and longest list.
+template <int TP, int NT>
+__device__ __forceinline__ void list_rounds(const SysConst &cg, const SysPtrs &p, int w, int g, unsigned short *stage,
+                            const float *s_cs2, const float4 *tpos, const unsigned *cstart, int &kept, int &longest) {
+  constexpr int NW = NT / 64;
+  __shared__ int s_cnt[2][kRoundSlots], s_seg[2][2][65], s_nseg[2][2], s_kmax[2], s_next[2];
+  // the constants used below, in registers: through the replica's descriptor in memory
+  // they would be read again after every store
+  SysConst c;
+  c.n = cg.n;
+  c.ntypes = cg.ntypes;
+  c.nvp = cg.nvp;
+  c.n_max = cg.n_max;
+  c.tp = TP;
+  c.tp_shift = cg.tp_shift;
+  c.full_axis = cg.full_axis;
+  c.tiles[0] = c.tiles[1] = 1;  // small systems: row-major cells
+  for (int k = 0; k < 3; ++k) {
+    c.nc[k] = cg.nc[k];
+    c.L[k] = cg.L[k];
+    c.invL[k] = cg.invL[k];
+    c.halfL[k] = cg.halfL[k];
+    c.cscale[k] = cg.cscale[k];
+  }
+  int *const nbl = p.nbl, *const nnb = p.nnb;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int nmax = c.n_max;
+  unsigned short *cand = stage + kRoundSlots * kRoundRow + wv * kCellWindow;
+  // the pieces of the round at T0, by waves 0 and 1 (64 slots each): one starts where the
+  // cell changes and after every kCellPiece slots
+  auto cut = [&](int T0, int par) {
+    if (wv < 2) {
+      const int l = 64 * wv + lane, m = c.n - T0;
+      int cell = -1;
+      if (l < m) {
+        int cx, cy, cz;
+        cell_coords(tpos[T0 + l], c, cx, cy, cz);
+        cell = (cz * c.nc[1] + cy) * c.nc[0] + cx;
+      }
+      s_cnt[par][l] = 0;
+      const int prev = __shfl_up(cell, 1, 64);
+      const unsigned long long first = __ballot(l < m && (lane == 0 || prev != cell));
+      const int since = lane - (63 - __builtin_clzll((first & ((2ull << lane) - 1ull)) | 1ull));
+      const bool head = l < m && since % kCellPiece == 0;
+      const unsigned long long hm = __ballot(head);
+      if (head) s_seg[par][wv][__popcll(hm & ((1ull << lane) - 1ull))] = l;
+      if (lane == 0) {
+        s_nseg[par][wv] = __popcll(hm);
+        s_seg[par][wv][__popcll(hm)] = min(64 * (wv + 1), max(m, 64 * wv));
+        s_kmax[par] = 0;
+        s_next[par] = NW;
+      }
+    }
+  };
+  int T0 = w * kRoundSlots, par = 0;
+  if (T0 < c.n) cut(T0, 0);
+  __syncthreads();
+  for (; T0 < c.n; T0 += g * kRoundSlots, par ^= 1) {
+    const int n0 = s_nseg[par][0], nseg = n0 + s_nseg[par][1];
+    auto sink = [&](int i, int k, int upto, int j) {
+      unsigned short *row = stage + (i - T0) * kRoundRow;
+      if (upto <= kCellStage)
+        row[k] = (unsigned short)j;
+      else if (k < kCellStage)
+        row[k] = (unsigned short)j;
+      else if (k < nmax)
+        nbl[nbl_addr(i, k, c)] = j;
+    };
+    for (int sg = wv; sg < nseg;) {
+      const int h = sg >= n0, q = sg - (h ? n0 : 0);
+      const int l0 = s_seg[par][h][q], l1 = s_seg[par][h][q + 1];
+      int cx, cy, cz;
+      cell_coords(tpos[T0 + l0], c, cx, cy, cz);
+      list_cell_particles(c, p, cx, cy, cz, T0 + l0, T0 + l1, cand, s_cnt[par] + l0, s_cs2, tpos, cstart, sink);
+      if (lane < l1 - l0) atomicMax(&s_kmax[par], s_cnt[par][l0 + lane]);
+      if (lane == 0) sg = atomicAdd(&s_next[par], 1);
+      sg = __builtin_amdgcn_readfirstlane(sg);
+    }
+    __syncthreads();
+    if (T0 + g * kRoundSlots < c.n) cut(T0 + g * kRoundSlots, par ^ 1);
+    const int m = min(kRoundSlots, c.n - T0);
+    const int kst = min(min(s_kmax[par], nmax), kCellStage);
+    const int groups = (kst + TP - 1) / TP;
+    for (int j = tid; j < groups * kRoundSlots * TP; j += NT) {
+      const int gr = j / (kRoundSlots * TP), rr = j % (kRoundSlots * TP), l = rr / TP, k = gr * TP + rr % TP;
+      if (l < m && k < min(s_cnt[par][l], kst))
+        nbl[(long long)gr * ((long long)c.nvp * TP) + (long long)T0 * TP + rr] = stage[l * kRoundRow + k];
+    }
+    if (tid < m) {
+      const int cn = s_cnt[par][tid];
+      longest = max(longest, cn);
+      kept += min(cn, nmax);
+      nnb[T0 + tid] = min(cn, nmax);
+    }
+    __syncthreads();
   }
 }
 
@@ -3037,7 +3245,7 @@ __device__ __forceinline__ void fill_positions(float4 *dst, const float4 *src, i
 // k_finish (so the thermostat needs no second barrier); piece 0 alone writes the
 // record and the control block.  The rebuild decision travels with the barrier.  On
 // a step that decides a rebuild, piece 0 sorts (as k_finish does), a barrier follows,
-// the pieces build the lists of particles wave, wave + 8g, ..., and another barrier
+// the pieces build the lists of particles wave, wave + NW g, ... (or rounds of cells), and another barrier
 // follows.  A system follows its single-system trajectory bit for bit at the same
 // (tp, ppb), whatever the pieces and the other jobs of its workgroups.
 //
@@ -3045,20 +3253,27 @@ __device__ __forceinline__ void fill_positions(float4 *dst, const float4 *src, i
 // from device memory rather than LDS.  Its spatial sort is the four-phase counting
 // sort of the launch chain, run by all pieces at the start of a step that rebuilds,
 // with a grid barrier after each phase.
-// Waves per SIMD the persistent kernel is compiled for: three from 16 lanes per
-// particle up (measured +12 % at KA 4096, 32 bytes of spills), the register count's
-// own two below, where three would spill 150 bytes per lane (the replica batch at
-// t_p = 1 measured 1 % slower).
-template <int TP>
+// Waves per SIMD the persistent kernel is compiled for: in a batch (kBatchThreads) the
+// four of its workgroup; else three from 16 lanes per particle up (measured +12 % at
+// KA 4096, 32 bytes of spills), the register count's own two below, where three would
+// spill 150 bytes per lane.
+template <int TP, int NT>
 struct kMultiWaves {
-  static constexpr int value = TP >= 16 ? 3 : 1;
+  static constexpr int value = NT == kBatchThreads ? NT / 256 : TP >= 16 ? 3 : 1;
 };
 
-template <int TP, int METHOD, bool BIG>
-__global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(kMultiWaves<TP>::value))) void k_multi(const ReplicaDesc *__restrict__ reps,
-                                                         const CoopJob *__restrict__ jobs,
-                                                         const int *__restrict__ job_off, int nsteps,
-                                                         int lds_bytes) {
+// List entries in flight per lane: four waves per SIMD hide the loads of four (4, 6 and 8
+// measure the same on the replica batch; eight spill more).
+template <int TP, int NT>
+struct kMultiBatch {
+  static constexpr int value = NT == kBatchThreads ? 4 : Batch<TP>::value;
+};
+
+template <int TP, int METHOD, bool BIG, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kMultiWaves<TP, NT>::value))) void k_multi(
+    const ReplicaDesc *__restrict__ reps, const CoopJob *__restrict__ jobs, const int *__restrict__ job_off, int nsteps,
+    int lds_bytes) {
+  constexpr int NW = NT / 64;
   extern __shared__ float4 s_dyn[];
   __shared__ SharedPairs sp;
   __shared__ BlockPartial s_waves[16];
@@ -3105,7 +3320,7 @@ __global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(k
       if (tid == 0) s_bit = 0;
       __syncthreads();
       if (BIG && rebuild) {  // the counting sort of the launch chain, phase by phase
-        const int base = J.w * kBatchThreads, stride = J.g * kBatchThreads;
+        const int base = J.w * NT, stride = J.g * NT;
         sort_bin(c, p, cur, base, stride);
         if (!coop_barrier(p.bar_flags, J.g, J.w, ++k, 0, p.ctl, &s_ok, &s_any)) return;
         if (J.w == 0 && tid == 0) begin_build(p.ctl);
@@ -3120,13 +3335,13 @@ __global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(k
         // all pairs from the positions of the step in LDS, no cells; after a periodic
         // re-sort from the sorted copy, with this piece's slots moved into place
         const bool resorted = s_resorted[j] != 0;
-        fill_positions(s_dyn, resorted ? p.t_pos : p.pos[cur], c.n);
+        fill_positions<NT>(s_dyn, resorted ? p.t_pos : p.pos[cur], c.n);
         if (resorted)
-          for (int t = J.w * kBatchThreads + tid; t < c.n; t += J.g * kBatchThreads)
+          for (int t = J.w * NT + tid; t < c.n; t += J.g * NT)
             place_sorted(p, cur, t, gload(p.t_pos, t));
         __syncthreads();
         int kept = 0, longest = 0;
-        for (int t = J.w * kBatchWaves + wv; t < c.n; t += J.g * kBatchWaves) {
+        for (int t = J.w * NW + wv; t < c.n; t += J.g * NW) {
           const int kt = list_allpairs_one(c, p, t, s_cs2, s_dyn, longest);
           if (lane == 0) kept += kt;
         }
@@ -3137,38 +3352,47 @@ __global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(k
         // the sorted positions and the cell starts go to LDS when they fit beside the
         // candidate windows, so the list build reads no device memory but its own list
         const int cs_words = (c.ncell + 1 + 3) & ~3;
-        const bool in_lds = !BIG && 16 * c.n + 4 * cs_words + 4 * kBatchWaves * kWaveCand <= lds_bytes;
+        // by cells when each wave gets several; with about one cell per wave the most
+        // crowded cell would set the pace, so then one wave per particle
+        const bool by_cell = 4 * J.g * NW <= c.ncell;
+        constexpr bool kRounds = !BIG && NT == kBatchThreads;
+        const int list_lds = kRounds && by_cell ? round_list_bytes(NT) : 4 * NW * kWaveCand;
+        const bool in_lds = !BIG && 16 * c.n + 4 * cs_words + list_lds <= lds_bytes;
         const float4 *tpos = p.t_pos;
         const unsigned *cstart = p.cell_start;
-        unsigned *cand = reinterpret_cast<unsigned *>(s_dyn) + wv * kWaveCand;
+        unsigned *list_area = reinterpret_cast<unsigned *>(s_dyn);
         if (in_lds) {
-          fill_positions(s_dyn, p.t_pos, c.n);
+          fill_positions<NT>(s_dyn, p.t_pos, c.n);
           unsigned *s_cs = reinterpret_cast<unsigned *>(s_dyn + c.n);
-          for (int q = tid; q <= c.ncell; q += kBatchThreads) s_cs[q] = gload((const int *)p.cell_start, q);
+          for (int q = tid; q <= c.ncell; q += NT) s_cs[q] = gload((const int *)p.cell_start, q);
           __syncthreads();
           tpos = s_dyn;
           cstart = s_cs;
-          cand = s_cs + cs_words + wv * kWaveCand;
+          list_area = s_cs + cs_words;
         }
+        unsigned *cand = list_area + wv * kWaveCand;
         // this piece's slots of the sorted arrays into place, coalesced (the list
         // build below only reads the sorted copies)
-        for (int t = J.w * kBatchThreads + tid; t < c.n; t += J.g * kBatchThreads)
+        for (int t = J.w * NT + tid; t < c.n; t += J.g * NT)
           place_sorted(p, cur, t, gload(p.t_pos, t));
-        // one wave per cell (list_cell_particles), cells dealt round-robin over the
-        // waves of all pieces, when each wave gets several cells; with about one cell
-        // per wave the most crowded cell would set the pace, so then one wave per
-        // particle.  The second half of the wave's window holds the counts.
+        // one wave per cell (list_cell_particles), cells dealt round-robin over the waves
+        // of all pieces, in a batch by rounds (list_rounds); or one wave per particle.  The
+        // second half of the wave's window holds the counts.
         int kept = 0, longest = 0;
-        const bool by_cell = 4 * J.g * kBatchWaves <= c.ncell;
         int *wcnt = reinterpret_cast<int *>(cand + kCellWindow);
-        auto direct = [&](int i, int kk, int jj) {
+        auto direct = [&](int i, int kk, int, int jj) {
           if (kk < c.n_max) p.nbl[nbl_addr(i, kk, c)] = jj;
         };
-        for (int t = J.w * kBatchWaves + wv; !by_cell && t < c.n; t += J.g * kBatchWaves) {
+        for (int t = J.w * NW + wv; !by_cell && t < c.n; t += J.g * NW) {
           const int kt = list_wave_one<false>(c, p, cur, t, cand, s_cs2, tpos, cstart, longest);
           if (lane == 0) kept += kt;
         }
-        for (int cell = J.w * kBatchWaves + wv; by_cell && cell < c.ncell; cell += J.g * kBatchWaves) {
+        if constexpr (kRounds) {
+          if (by_cell)
+            list_rounds<TP, NT>(c, p, J.w, J.g, reinterpret_cast<unsigned short *>(list_area), s_cs2, tpos, cstart, kept,
+                                longest);
+        }
+        for (int cell = J.w * NW + wv; !kRounds && by_cell && cell < c.ncell; cell += J.g * NW) {
           const unsigned e1 = min(cstart[cell + 1], (unsigned)c.n), e0 = min(cstart[cell], e1);
           const int ne = (int)(e1 - e0);
           if (ne == 0) continue;  // uniform over the wave
@@ -3193,7 +3417,7 @@ __global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(k
         list_tally(kept, longest, c.n_max, p.ctl);
         if (!coop_barrier(p.bar_flags, J.g, J.w, ++k, 0, p.ctl, &s_ok, &s_any)) return;
       }
-      if (!BIG && !prefilled) fill_positions(s_dyn, p.pos[cur], c.n);
+      if (!BIG && !prefilled) fill_positions<NT>(s_dyn, p.pos[cur], c.n);
       prefilled = false;
       __syncthreads();
       // positions of the step: the LDS copy, or device memory for a large system
@@ -3210,7 +3434,7 @@ __global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(k
       // the system's partials buffer (indexed by the unit)
       const bool wp_lds = my_units <= kLdsUnits;
       BlockPartial *wpart = p.part + 2 * G;
-      for (int q = wv; q < my_units; q += kBatchWaves) {
+      for (int q = wv; q < my_units; q += NW) {
         const int b = J.w + (q / wpv) * J.g;
         const int u = b * wpv + q % wpv;
         const int gt = u * 64 + lane;
@@ -3229,7 +3453,8 @@ __global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(k
             l0 = gload(p.last, i);
           }
         }
-        force_lane<TP, METHOD, Batch<TP>::value, false>(ic, t, active, pi, spos, nblg, nnbg, sp, c, fx, fy, fz, uu, w);
+        force_lane<TP, METHOD, kMultiBatch<TP, NT>::value, false>(ic, t, active, pi, spos, nblg, nnbg, sp, c, fx, fy, fz,
+                                                                  uu, w);
         fx = lane_sum<TP>(fx);
         fy = lane_sum<TP>(fy);
         fz = lane_sum<TP>(fz);
@@ -3249,7 +3474,7 @@ __global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(k
       }
       __syncthreads();
       // owned block partials: each block's waves in index order (as group_reduce)
-      for (int r = tid; r < my_blocks; r += kBatchThreads) {
+      for (int r = tid; r < my_blocks; r += NT) {
         const int b = J.w + r * J.g;
         BlockPartial a = wp_lds ? s_wp[r * wpv] : wpart[b * wpv];
         for (int q = 1; q < wpv; ++q) fold(a, wp_lds ? s_wp[r * wpv + q] : wpart[b * wpv + q]);
@@ -3260,7 +3485,7 @@ __global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(k
       CtlView cv{};
       if (J.w == 0 && tid == 0) cv = load_ctl(p.ctl);
       // every piece: the reduction of k_finish (1024 threads, each thread here
-      // standing in for threads tid and tid + 512 of that workgroup); with at most
+      // standing in for threads tid and tid + NT of that workgroup); with at most
       // 1024 blocks each thread's partials are loaded first, so that the positions
       // of the next step (loaded now when no rebuild is due and this is the
       // workgroup's only job) arrive in the same round trip
@@ -3268,21 +3493,21 @@ __global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(k
       if (G <= 1024) {
         BlockPartial q0 = zero_partial(), q1 = zero_partial();
         if (tid < G) q0 = bpart[tid];
-        if (tid + kBatchThreads < G) q1 = bpart[tid + kBatchThreads];
+        if (NT < 1024 && tid + NT < G) q1 = bpart[tid + NT];
         prefilled = !BIG && nj == 1 && !s_any && step + 1 < nsteps;
-        if (prefilled) fill_positions(s_dyn, p.pos[cur ^ 1], c.n);
+        if (prefilled) fill_positions<NT>(s_dyn, p.pos[cur ^ 1], c.n);
         if (tid < G) fold(a0, q0);
-        if (tid + kBatchThreads < G) fold(a1, q1);
+        if (NT < 1024 && tid + NT < G) fold(a1, q1);
       } else {
         for (int b = tid; b < G; b += 1024) fold(a0, bpart[b]);
-        for (int b = tid + kBatchThreads; b < G; b += 1024) fold(a1, bpart[b]);
+        for (int b = tid + NT; NT < 1024 && b < G; b += 1024) fold(a1, bpart[b]);
       }
       // a wave with no blocks holds zero partials, whose butterfly gives zeros again
       if (wv * 64 < G) wave_reduce(a0);
-      if (kBatchThreads + wv * 64 < G) wave_reduce(a1);
+      if (NT < 1024 && NT + wv * 64 < G) wave_reduce(a1);
       if (lane == 0) {
         s_waves[wv] = a0;
-        s_waves[wv + kBatchWaves] = a1;
+        if (NT < 1024) s_waves[wv + NW] = a1;
       }
       __syncthreads();
       if (tid == 0) {
@@ -3328,14 +3553,14 @@ __global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(k
   }
 }
 
-template <int TP, bool BIG>
+template <int TP, bool BIG, int NT>
 const void *multi_fn(int method) {
-  return method == 0 ? (const void *)k_multi<TP, 0, BIG>
-         : method == 1 ? (const void *)k_multi<TP, 1, BIG>
-         : method == 2 ? (const void *)k_multi<TP, 2, BIG>
-         : method == 3 ? (const void *)k_multi<TP, 3, BIG>
-         : method == 4 ? (const void *)k_multi<TP, 4, BIG>
-                       : (const void *)k_multi<TP, 5, BIG>;
+  return method == 0 ? (const void *)k_multi<TP, 0, BIG, NT>
+         : method == 1 ? (const void *)k_multi<TP, 1, BIG, NT>
+         : method == 2 ? (const void *)k_multi<TP, 2, BIG, NT>
+         : method == 3 ? (const void *)k_multi<TP, 3, BIG, NT>
+         : method == 4 ? (const void *)k_multi<TP, 4, BIG, NT>
+                       : (const void *)k_multi<TP, 5, BIG, NT>;
 }
 
 // ---------------------------------------------------------------- start of a stepping call
@@ -3620,11 +3845,14 @@ hipError_t launch_force_tp(int method, dim3 g, dim3 b, hipStream_t st, const Sys
   PREFIX template hipError_t launch_step_tp<TP>(int, int, dim3, dim3, hipStream_t, const SysConst &, const SysPtrs &,   \
                                                 int, int, size_t);                                                      \
   PREFIX template hipError_t launch_force_tp<TP>(int, dim3, dim3, hipStream_t, const SysConst &, const SysPtrs &, int); \
-  PREFIX template const void *multi_fn<TP, false>(int);
+  PREFIX template const void *multi_fn<TP, false, kPersistThreads>(int);
+#define SRMD_KERNELS_TO_8(PREFIX, TP)                                     \
+  PREFIX template const void *multi_fn<TP, true, kPersistThreads>(int);   \
+  PREFIX template const void *multi_fn<TP, false, kBatchThreads>(int);
 #ifdef SRMD_TP
 SRMD_KERNELS_OF(, SRMD_TP)
 #if SRMD_TP <= 8
-template const void *multi_fn<SRMD_TP, true>(int);
+SRMD_KERNELS_TO_8(, SRMD_TP)
 #endif
 #else
 SRMD_KERNELS_OF(extern, 1)
@@ -3634,57 +3862,73 @@ SRMD_KERNELS_OF(extern, 8)
 SRMD_KERNELS_OF(extern, 16)
 SRMD_KERNELS_OF(extern, 32)
 SRMD_KERNELS_OF(extern, 64)
-extern template const void *multi_fn<1, true>(int);
-extern template const void *multi_fn<2, true>(int);
-extern template const void *multi_fn<4, true>(int);
-extern template const void *multi_fn<8, true>(int);
+SRMD_KERNELS_TO_8(extern, 1)
+SRMD_KERNELS_TO_8(extern, 2)
+SRMD_KERNELS_TO_8(extern, 4)
+SRMD_KERNELS_TO_8(extern, 8)
 
-// The persistent kernel for (tp, method); the large-system form exists for tp <= 8.
-static const void *multi_fn_of(int tp, int method, bool big) {
+// The persistent kernel for (tp, method) with a workgroup of threads; the large-system
+// form exists for tp <= 8.
+static const void *multi_fn_of(int tp, int method, bool big, int threads) {
   if (big) {
     switch (tp) {
-      case 1: return multi_fn<1, true>(method);
-      case 2: return multi_fn<2, true>(method);
-      case 4: return multi_fn<4, true>(method);
-      case 8: return multi_fn<8, true>(method);
+      case 1: return multi_fn<1, true, kPersistThreads>(method);
+      case 2: return multi_fn<2, true, kPersistThreads>(method);
+      case 4: return multi_fn<4, true, kPersistThreads>(method);
+      case 8: return multi_fn<8, true, kPersistThreads>(method);
+      default: return nullptr;
+    }
+  }
+  if (threads == kBatchThreads) {
+    switch (tp) {
+      case 1: return multi_fn<1, false, kBatchThreads>(method);
+      case 2: return multi_fn<2, false, kBatchThreads>(method);
+      case 4: return multi_fn<4, false, kBatchThreads>(method);
+      case 8: return multi_fn<8, false, kBatchThreads>(method);
       default: return nullptr;
     }
   }
   switch (tp) {
-    case 1: return multi_fn<1, false>(method);
-    case 2: return multi_fn<2, false>(method);
-    case 4: return multi_fn<4, false>(method);
-    case 8: return multi_fn<8, false>(method);
-    case 16: return multi_fn<16, false>(method);
-    case 32: return multi_fn<32, false>(method);
-    case 64: return multi_fn<64, false>(method);
+    case 1: return multi_fn<1, false, kPersistThreads>(method);
+    case 2: return multi_fn<2, false, kPersistThreads>(method);
+    case 4: return multi_fn<4, false, kPersistThreads>(method);
+    case 8: return multi_fn<8, false, kPersistThreads>(method);
+    case 16: return multi_fn<16, false, kPersistThreads>(method);
+    case 32: return multi_fn<32, false, kPersistThreads>(method);
+    case 64: return multi_fn<64, false, kPersistThreads>(method);
     default: return nullptr;
   }
 }
 
-bool multi_big_supported(int tp) { return multi_fn_of(tp, 0, true) != nullptr; }
+bool multi_big_supported(int tp) { return multi_fn_of(tp, 0, true, kPersistThreads) != nullptr; }
+
+// Threads of a workgroup of the persistent kernel for a batch.
+int batch_threads(int tp) { return tp <= kBatchMaxTp ? kBatchThreads : kPersistThreads; }
+
+int persist_threads() { return kPersistThreads; }
 
 // Launch k_multi over nwg workgroups.  cooperative: some system is split over
 // several workgroups, which must then all be resident at once.
-hipError_t launch_multi(int tp, int method, bool big, int nwg, size_t lds, hipStream_t st, const ReplicaDesc *reps,
-                        const CoopJob *jobs, const int *job_off, int nsteps, bool cooperative) {
-  const void *fn = multi_fn_of(tp, method, big);
+hipError_t launch_multi(int tp, int method, bool big, int threads, int nwg, size_t lds, hipStream_t st,
+                        const ReplicaDesc *reps, const CoopJob *jobs, const int *job_off, int nsteps,
+                        bool cooperative) {
+  const void *fn = multi_fn_of(tp, method, big, threads);
   if (!fn || nwg < 1) return hipErrorInvalidValue;
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   int lds_bytes = (int)lds;
   void *args[] = {&reps, &jobs, &job_off, &nsteps, &lds_bytes};
-  if (cooperative) return hipLaunchCooperativeKernel(fn, dim3(nwg), dim3(kBatchThreads), args, (unsigned)lds, st);
-  return hipLaunchKernel(fn, dim3(nwg), dim3(kBatchThreads), args, lds, st);
+  if (cooperative) return hipLaunchCooperativeKernel(fn, dim3(nwg), dim3(threads), args, (unsigned)lds, st);
+  return hipLaunchKernel(fn, dim3(nwg), dim3(threads), args, lds, st);
 }
 
 // Workgroups of the persistent kernel the device holds at once (at most 256).
-int multi_max_groups(int tp, int method, bool big, size_t lds) {
-  const void *fn = multi_fn_of(tp, method, big);
+int multi_max_groups(int tp, int method, bool big, int threads, size_t lds) {
+  const void *fn = multi_fn_of(tp, method, big, threads);
   if (!fn) return 0;
   if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return 0;
   int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kBatchThreads, lds) != hipSuccess) return 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds) != hipSuccess) return 0;
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
@@ -3696,12 +3940,15 @@ int multi_max_jobs() { return kMaxJobs; }
 // Dynamic LDS of the persistent kernel: the positions of a step, the sort's scratch,
 // and where it fits in 150 KiB, the list build's copies of the sorted positions and
 // the cell starts beside the candidate windows (up to 4096 cells counted).
-size_t batch_lds_bytes(int n_max_particles) {
+size_t multi_lds_bytes(int n_max_particles, int threads) {
   const size_t pos = 16 * (size_t)n_max_particles;
   const size_t scratch = 4 * (size_t)(kSmallCells + 1 + kSmallN);
-  const size_t cand = 4 * (size_t)(kBatchWaves * kWaveCand);
-  const size_t listing = pos + 4 * (size_t)(4096 + 4) + cand;
+  const size_t cand = 4 * (size_t)(threads / 64 * kWaveCand);
   size_t b = std::max(pos, std::max(scratch, cand));
+  // a batch's workgroup has a compute unit to itself: as much as its other arrays leave
+  if (threads == kBatchThreads)
+    return std::max(b, std::min<size_t>(146 * 1024, pos + 4 * (size_t)(kSmallCells + 4) + cand));
+  const size_t listing = pos + 4 * (size_t)(4096 + 4) + cand;
   if (listing <= 150 * 1024) b = std::max(b, listing);
   return b;
 }
@@ -3709,7 +3956,7 @@ size_t batch_lds_bytes(int n_max_particles) {
 int batch_max_particles() { return kSmallN; }
 
 // Dynamic LDS of the large-system persistent kernel: the list build's candidate windows.
-size_t big_lds_bytes() { return 4 * (size_t)(kBatchWaves * kWaveCand); }
+size_t big_lds_bytes() { return 4 * (size_t)(kPersistThreads / 64 * kWaveCand); }
 
 int stage_units(int n) { return (n + kStageSlots - 1) / kStageSlots; }
 

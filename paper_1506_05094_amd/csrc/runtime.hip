@@ -42,11 +42,14 @@ hipError_t launch_direct_init(hipStream_t st, const SysConst &c, const SysPtrs &
 hipError_t launch_direct_out(hipStream_t st, const SysConst &c, const SysPtrs &p, float *force, double *energy,
                              int *status);
 bool small_sort_fits(int n, int ncell);
-size_t batch_lds_bytes(int n_max_particles);
+size_t multi_lds_bytes(int n_max_particles, int threads);
+int batch_threads(int tp);
+int persist_threads();
 int batch_max_particles();
-hipError_t launch_multi(int tp, int method, bool big, int nwg, size_t lds, hipStream_t st, const ReplicaDesc *reps,
-                        const CoopJob *jobs, const int *job_off, int nsteps, bool cooperative);
-int multi_max_groups(int tp, int method, bool big, size_t lds);
+hipError_t launch_multi(int tp, int method, bool big, int threads, int nwg, size_t lds, hipStream_t st,
+                        const ReplicaDesc *reps, const CoopJob *jobs, const int *job_off, int nsteps,
+                        bool cooperative);
+int multi_max_groups(int tp, int method, bool big, int threads, size_t lds);
 bool multi_big_supported(int tp);
 size_t big_lds_bytes();
 int multi_max_jobs();
@@ -372,7 +375,7 @@ srmd_status flush_host_sort(srmd_system *s) {
 int step_blocks(const srmd_system *s) { return (int)(((long long)s->n * s->tp + s->tp * s->ppb - 1) / (s->tp * s->ppb)); }
 
 // Dynamic LDS of the persistent kernel for this system.
-size_t persist_lds(const srmd_system *s) { return s->c.small_sort ? batch_lds_bytes(s->n) : big_lds_bytes(); }
+size_t persist_lds(const srmd_system *s) { return s->c.small_sort ? multi_lds_bytes(s->n, persist_threads()) : big_lds_bytes(); }
 
 // Workgroups of the persistent kernel (0: launch chains): by default one workgroup
 // of 512 threads per 8 waves of the step launch, so each wave takes one wave of it.
@@ -391,7 +394,7 @@ void resolve_persistent(srmd_system *s) {
   }
   const int threads = s->tp * s->ppb;
   const int units = step_blocks(s) * (threads / 64);
-  const int cap = multi_max_groups(s->tp, kmethod(s), !s->c.small_sort, persist_lds(s));
+  const int cap = multi_max_groups(s->tp, kmethod(s), !s->c.small_sort, persist_threads(), persist_lds(s));
   int want = preq > 0 ? preq : std::max(1, (units + 7) / 8);
   if (preq < 0) want = std::min(want, cap);
   if (want > cap || want < 1)
@@ -825,7 +828,7 @@ srmd_status launch_persistent(srmd_system *s, int cnt) {
   srmd_status sl = plain_lists(s, true);
   if (sl != SRMD_OK) return sl;
   if (g > 1) HIPCHK(s, hipMemsetAsync(s->p.bar_flags, 0, sizeof(unsigned) * 2 * 256, s->stream));
-  HIPCHK(s, launch_multi(s->tp, kmethod(s), !s->c.small_sort, g, persist_lds(s), s->stream, s->d_desc, s->d_jobs, s->d_job_off,
+  HIPCHK(s, launch_multi(s->tp, kmethod(s), !s->c.small_sort, persist_threads(), g, persist_lds(s), s->stream, s->d_desc, s->d_jobs, s->d_job_off,
                          cnt, g > 1));
   s->cur ^= (cnt & 1);
   return SRMD_OK;
@@ -1255,12 +1258,20 @@ srmd_status batch_plan(srmd_batch *b, int W) {
   return SRMD_OK;
 }
 
+// Dynamic LDS of the batch's launches at tp threads per particle.
+size_t batch_lds(const srmd_batch *b, int tp) {
+  int nmax = 0;
+  for (auto *s : b->sys) nmax = std::max(nmax, s->n);
+  return multi_lds_bytes(nmax, batch_threads(tp));
+}
+
 // Descriptors and workgroup plan of the batch for the systems' current launch shapes
 // (all replicas share b->tp).
 srmd_status batch_replan(srmd_batch *b) {
   srmd_status st = batch_sync_desc(b);
   if (st != SRMD_OK) return st;
-  int W = multi_max_groups(b->tp, b->method, false, b->lds);
+  b->lds = batch_lds(b, b->tp);
+  int W = multi_max_groups(b->tp, b->method, false, batch_threads(b->tp), b->lds);
   if (b->max_wg > 0) W = std::min(W, b->max_wg);
   if (W < 1) return bfail(b, SRMD_EUNSUPPORTED, "the persistent kernel does not fit on the device");
   return batch_plan(b, W);
@@ -2989,9 +3000,6 @@ srmd_status srmd_batch_create_limited(srmd_batch **out, srmd_system *const *syst
   b->stream = systems[0]->stream;
   b->tp = systems[0]->tp;
   b->method = kmethod(systems[0]);
-  int nmax = 0;
-  for (auto *s : b->sys) nmax = std::max(nmax, s->n);
-  b->lds = batch_lds_bytes(nmax);
   b->host_desc.assign((size_t)count, ReplicaDesc{});
   std::memset(b->host_desc.data(), 0xff, sizeof(ReplicaDesc) * (size_t)count);  // forces the first upload
   b->desc_buf = raw_alloc(sizeof(ReplicaDesc) * (size_t)count);
@@ -3044,7 +3052,7 @@ srmd_status srmd_batch_step(srmd_batch *b, int64_t nsteps, int32_t thermo_every,
     // launches of kPersistChunk steps (an even count: every launch starts on the
     // position buffer of the call start, which the descriptors hold)
     const int cnt = (int)std::min<long long>(kPersistChunk, nsteps - done);
-    e = launch_multi(b->tp, b->method, false, b->nwg, b->lds, b->stream, b->d_desc, b->d_jobs, b->d_job_off, cnt,
+    e = launch_multi(b->tp, b->method, false, batch_threads(b->tp), b->nwg, b->lds, b->stream, b->d_desc, b->d_jobs, b->d_job_off, cnt,
                      b->cooperative);
     if (e == hipSuccess && done + cnt < nsteps)
       for (size_t r = 0; r < b->sys.size() && e == hipSuccess; ++r)
@@ -3134,7 +3142,7 @@ srmd_status srmd_batch_autotune(srmd_batch *b, int32_t steps_per_trial, int32_t 
   // a row slower than the best, or one 5 % slower, or a resource limit
   int worse = 0;
   for (int tp = 1; tp <= 64; tp *= 2) {
-    if (!multi_max_groups(tp, b->method, false, b->lds)) break;
+    if (!multi_max_groups(tp, b->method, false, batch_threads(tp), batch_lds(b, tp))) break;
     double ms;
     srmd_status st = trial(tp, thr, &ms);
     if (st != SRMD_OK) return st;
