@@ -37,9 +37,9 @@ hipError_t launch_stage_expand(hipStream_t st, const SysConst &c, const SysPtrs 
 hipError_t launch_arm(hipStream_t st, Control *ctl, int cur, long long nsteps);
 hipError_t launch_state_out(hipStream_t st, const SysPtrs &p, int n, int cur, const StateXfer &o);
 hipError_t launch_state_in(hipStream_t st, const SysPtrs &p, int n, int cur, const float L[3], const StateXfer &in);
-hipError_t launch_direct_init(hipStream_t st, const SysConst &c, const SysPtrs &p, const float *xyz, const int *type,
+hipError_t launch_direct_sort(hipStream_t st, const SysConst &c, const SysPtrs &p, const float *xyz, const int *type,
                               int *status);
-hipError_t launch_direct_out(hipStream_t st, const SysConst &c, const SysPtrs &p, float *force, double *energy,
+hipError_t launch_direct_out(hipStream_t st, const SysConst &c, const SysPtrs &p, int G, float *force, double *energy,
                              int *status);
 bool small_sort_fits(int n, int ncell);
 size_t multi_lds_bytes(int n_max_particles, int threads);
@@ -3322,7 +3322,6 @@ extern "C" srmd_status srmd_compute_forces_noalloc(const srmd_lj_config *cfg, co
   p.cell_start = cv.take<unsigned>((size_t)c.ncell + 1);
   p.part = cv.take<BlockPartial>((size_t)blocks);
   p.ctl = cv.take<Control>(1);
-  p.thermo = cv.take<Thermo>(1);
   // the list takes what is left, as many rows as fit (at most one per particle)
   const size_t used = (cv.off + 255) & ~(size_t)255;
   if (used >= kDirectScratchBytes) return fail(nullptr, SRMD_EUNSUPPORTED, "system too large for the scratch array");
@@ -3337,11 +3336,9 @@ extern "C" srmd_status srmd_compute_forces_noalloc(const srmd_lj_config *cfg, co
   auto chk = [&](hipError_t e, const char *what) {
     return e == hipSuccess ? SRMD_OK : fail(nullptr, SRMD_EHIP, std::string(what) + ": " + hipGetErrorString(e));
   };
-  if ((st = chk(launch_direct_init(stream, c, p, d_pos, d_type, d_status), "set-up kernel")) != SRMD_OK) return st;
-  if ((st = chk(launch_host_sort(stream, c, p, 0), "spatial sort")) != SRMD_OK) return st;
+  if ((st = chk(launch_direct_sort(stream, c, p, d_pos, d_type, d_status), "spatial sort")) != SRMD_OK) return st;
   if ((st = chk(launch_rebuild(stream, c, p, 0), "list build")) != SRMD_OK) return st;
   if ((st = chk(launch_force(t.tp, (int)t.method, blocks, threads, stream, c, p, 0), "force kernel")) != SRMD_OK)
     return st;
-  if ((st = chk(launch_finish(1, blocks, 0, stream, c, p), "reduction")) != SRMD_OK) return st;
-  return chk(launch_direct_out(stream, c, p, d_force, d_energy, d_status), "output kernel");
+  return chk(launch_direct_out(stream, c, p, blocks, d_force, d_energy, d_status), "output kernel");
 }
