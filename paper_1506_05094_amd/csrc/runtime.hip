@@ -621,9 +621,19 @@ srmd_status prepare(srmd_system *s) {
       s->stage_alloc = s->p.stage_src ? units * (size_t)c.stage_cap : 0;
     }
     if (!s->p.stage_n) s->p.stage_n = (int *)dev_alloc(s, sizeof(int) * units);
-    if (!s->p.list16 || !s->p.stage_src || !s->p.stage_n)
-      return fail(s, SRMD_ENOMEM, "staged list allocation failed");
-    HIPCHK(s, hipMemsetAsync(s->p.stage_n, 0, sizeof(int) * units, s->stream));
+    if (s->p.list16 && s->p.stage_src && s->p.stage_n) {
+      HIPCHK(s, hipMemsetAsync(s->p.stage_n, 0, sizeof(int) * units, s->stream));
+    } else {  // no memory beside the plain lists (which bound the system's size): use those
+      dev_free(s, s->p.list16);
+      dev_free(s, s->p.stage_src);
+      dev_free(s, s->p.stage_n);
+      s->p.list16 = s->p.stage_src = nullptr;
+      s->p.stage_n = nullptr;
+      s->list16_alloc = 0;
+      s->stage_alloc = 0;
+      c.stage = 0;
+      (void)hipGetLastError();
+    }
   }
   resolve_persistent(s);
   drop_graphs(s);
