@@ -196,8 +196,10 @@ srmd_status srmd_set_launch(srmd_system *s, int32_t tp, int32_t ppb);
  * sort_mode: 0 automatic, 1 the spatial sort in one workgroup's LDS (systems of up
  * to 8192 particles and 8192 cells; larger ones fall back to 2), 2 the multi-kernel
  * counting sort.  list_mode: 0 automatic, 1 one wave per particle, 2 one thread per
- * particle (the paper's section 7 layout), 3 one wave per cell (the particles of a
- * cell share one load of their stencil's candidates), 4 all pairs (the paper's
+ * particle (the paper's section 7 layout; large systems at tp <= 4 and blocks of
+ * whole 256-particle units keep 16-bit lists into LDS copies of the units'
+ * neighbourhoods, built by two lanes per particle), 3 one wave per cell (the
+ * particles of a cell share one load of their stencil's candidates), 4 all pairs (the paper's
  * O(N^2) builder for small systems, section 6: every particle against every other
  * in index order, no cells and no spatial sort; systems of at most 8192 particles
  * and 8192 cells, sort_mode 0 or 1, else SRMD_EINVAL at the next step), 5 one
@@ -237,8 +239,8 @@ srmd_status srmd_set_sort_interval(srmd_system *s, int32_t builds);
 srmd_status srmd_set_fused_reduction(srmd_system *s, int32_t enable);
 
 /* Run the steps of a small system as persistent launches (one launch per 500
- * steps) instead of graph-captured launch chains (three launches per step).  Small systems are bound by latency, not by
- * arithmetic (section 3); the paper keeps their whole run on the device without
+ * steps) instead of graph-captured launch chains.  Small systems are bound by latency,
+ * not by arithmetic (section 3); the paper keeps their whole run on the device without
  * host round trips (section 6), and this mode also removes the launch boundaries
  * between the kernels of a step.  groups = 0: launch
  * chains (the default unless srmd_autotune chose otherwise); groups = -1: persistent,

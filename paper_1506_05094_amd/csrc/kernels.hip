@@ -8,20 +8,25 @@
 // lives on the device (the paper's device-side flag of section 6), so no step needs
 // the host:
 //   list rebuild, only when the flag is set (every kernel exits at once otherwise):
-//     small systems: the spatial sort already ran at the end of the previous step
-//                    (k_finish), so only the list kernel runs here;
+//     small systems: the spatial sort already ran at the end of the previous step, so
+//                    only the list build runs here, or inside k_step;
 //     large systems: k_bin (cells, arrival slots, tile counts), k_scan (cell
 //                    offsets, one workgroup per tile), k_scatter, k_gather
 //                    (deterministic rank by particle id, gather of every
 //                    per-particle array: the reorder of section 7), then the list
-//                    kernel;
-//     list kernels: k_list_wave (a wave per particle), k_list_cell (a wave per
-//                    cell), k_list_thread (a thread per particle), k_list_allpairs
-//                    (all pairs in index order, no sort: the O(N^2) builder of
-//                    section 6);
+//                    kernel.  A chain holds these once per 8 to 32 steps; a step
+//                    that finds a rebuild due exits, and so do those after it, up
+//                    to the next of these places;
+//     list kernels: k_list_wave (a wave per particle), k_list_cell (a wave per piece
+//                    of a cell), k_list_stage (16-bit lists into LDS copies of the
+//                    neighbourhoods of 256 particles, with k_stage_expand for their
+//                    readers outside the step), k_list_thread (a thread per
+//                    particle), k_list_row, k_list_allpairs (all pairs in index
+//                    order, no sort: the O(N^2) builder of section 6);
 //   k_step    pair forces with t_p lanes per particle (sections 3 and 5) fused with
-//             the leapfrog / Nose-Hoover update; float64 partial sums per block;
-//   k_finish  one workgroup: fixed-order float64 reduction of the partials,
+//             the leapfrog / Nose-Hoover update; float64 partial sums per block; its
+//             last workgroup (or k_finish, one workgroup, as a launch of its own)
+//             ends the step: fixed-order float64 reduction of the partials,
 //             thermostat update, thermodynamic record, the displacement test that
 //             sets the rebuild flag (section 6), and for small systems the whole
 //             spatial sort in LDS when a rebuild is due.
