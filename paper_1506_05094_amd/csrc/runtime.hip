@@ -1928,6 +1928,7 @@ srmd_status srmd_save_state(srmd_system *s, void *buf, size_t bytes, size_t *nee
   HIPCHK(s, hipMemcpyAsync(&h.ctl, s->p.ctl, sizeof(Control), hipMemcpyDeviceToHost, s->stream));
   HIPCHK(s, hipMemcpyAsync(&h.thermo, s->p.thermo, sizeof(Thermo), hipMemcpyDeviceToHost, s->stream));
   HIPCHK(s, hipStreamSynchronize(s->stream));
+  h.ctl.list_entries = h.ctl.entries;
   // the list is stored when it is the one the next force evaluation uses
   const long long rows = h.ctl.rebuild ? 0 : (h.ctl.max_nbrs + s->c.tp - 1) / s->c.tp;
   *needed = state_bytes(s, rows);
@@ -2025,6 +2026,7 @@ srmd_status srmd_load_state(srmd_system *s, const void *buf, size_t bytes) {
   if (keep_list && s->c.stage)  // the restored lists are plain ones
     HIPCHK(s, hipMemsetAsync(s->p.stage_n, 0, sizeof(int) * (size_t)stage_units(s->n), s->stream));
   Control c = h.ctl;
+  c.entries = c.list_entries;
   c.error = 0;
   if (!keep_list) {
     // the list is rebuilt (spatial sort first) before the next force evaluation; a
@@ -2103,7 +2105,7 @@ srmd_status srmd_get_stats(srmd_system *s, srmd_stats *out) {
   if (st != SRMD_OK) return st;
   out->steps = h.step;
   out->n_rebuilds = h.n_rebuilds;
-  out->list_entries = h.list_entries;
+  out->list_entries = h.entries;
   out->max_nbrs = h.max_nbrs;
   out->n_max = s->c.n_max;
   out->tp = s->tp;

@@ -102,7 +102,7 @@ struct Control {
   long long n_rebuilds;
   long long n_records;     // records written to the trace
   long long trace_cap;     // capacity of the device trace
-  long long list_entries;  // total entries of the current list
+  long long list_entries;  // as entries, in a saved state (its place in the files)
   double xi;               // Nose-Hoover friction at the current step
   double xi_int;           // its time integral
   unsigned long long prof_ticks;  // accumulated step-kernel durations (device clock ticks)
@@ -110,10 +110,15 @@ struct Control {
   int resorted;                   // all-pairs lists: the build ahead starts from a fresh spatial sort
   int cur;                        // position buffer of the next step
   long long stop;                 // run-ahead chains: no step beyond this step count
-  int pad[38];
+  int pad[36];
+  // Total entries of the current list.  The workgroups of a list build add to it; on
+  // another cache line than max_nbrs, which they raise, as the atomics of one line follow
+  // each other at about 10 ns.
+  long long entries;
 };
 
-static_assert(sizeof(Control) == 256, "control block layout");
+static_assert(sizeof(Control) == 256 && offsetof(Control, max_nbrs) < 128 && offsetof(Control, entries) >= 128,
+              "control block layout");
 
 // Thermo accumulators of the last force evaluation / step.
 struct Thermo {
