@@ -1461,9 +1461,9 @@ static __global__ __launch_bounds__(256) void k_list_allpairs(SysConst c, SysPtr
 
 constexpr int kListWaves = 16;  // waves (particles) per workgroup of k_list_wave
 
-// One wave per particle (list_wave_one).  The workgroups' tallies meet at one memory word
-// (about 10 ns each), so the workgroups are few and large: 1500 particles 15.6 us with 4
-// waves each, 11.7 with 8, 10.2 with 16.
+// One wave per particle (list_wave_one).  The workgroups' tallies queue at their memory
+// words (about 10 ns each), so the workgroups are few and large: 1500 particles 15.6 us
+// with 4 waves each, 11.7 with 8, 10.2 with 16 (both words on one cache line then).
 static __global__ __launch_bounds__(64 * kListWaves) void k_list_wave(SysConst c, SysPtrs p, int cur) {
   if (!rebuild_due(p.ctl, cur)) return;
   __shared__ float s_cs2[kMaxPairs];
@@ -2242,7 +2242,8 @@ constexpr int kCellStage = 128;  // list entries per particle staged in LDS
 // candidates' indices, then positions, then the tests), so the pieces are many and the
 // waves eight: with two waves and whole cells a wave took about seven cells of a liquid
 // one after the other (54 -> 27 us a build for the liquid of 16 000, 178 -> 115 for the
-// salt of 20 000, 50 -> 26 for the mixture of 5003).  The lists are staged in LDS as
+// salt of 20 000, 50 -> 26 for the mixture of 5003; 22, 97 and 23 with the image from the
+// cells and the tallies on two lines).  The lists are staged in LDS as
 // [particle][entry] and then written out by the workgroup in address order, so each
 // entry index of the column-major list is one contiguous span; entries past kCellStage
 // are written directly.
