@@ -1681,9 +1681,13 @@ __device__ __forceinline__ int stage_lists(const SysConst &c, const SysPtrs &p, 
   const int lane = threadIdx.x & 63, sub = lane % kStageLanes, col = lane / kStageLanes;
   const int ti = ptype(r), group = 2 * c.tp;
   const int nmax = c.n_max;
-  // the particle's own place in the copy: its cell is the stencil's centre
-  const int centre = v.cs[cell + (2 * R.Y + 2) * R.X + 2];
-  const int self = centre + (t - (int)((unsigned)__float_as_int(v.pos[centre].w) >> 2));
+  // the particle's own place in the copy: its cell is the stencil's centre, whose kept
+  // particles follow each other by slot; those before it that are not in the copy (in cells
+  // longer than the list radius) leave it earlier than the slots tell
+  auto slot_at = [&](int k) { return (int)((unsigned)__float_as_int(v.pos[k].w) >> 2); };
+  const int at0 = cell + (2 * R.Y + 2) * R.X + 2, centre = v.cs[at0];
+  int self = min(centre + (t - slot_at(centre)), v.cs[at0 + 1] - 1);
+  while (self > centre && slot_at(self) > t) --self;
   int count = 0;      // entries of the particle (the same in its lanes)
   int flushed = 0;    // uniform: every particle's entries below it are written (a multiple of group)
   bool spill = false; // this particle's entries are written directly
