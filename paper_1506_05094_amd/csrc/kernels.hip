@@ -1481,7 +1481,6 @@ static __global__ __launch_bounds__(64 * kListWaves) void k_list_wave(SysConst c
 }
 
 constexpr int kThreadBatch = 10;  // candidate positions in flight per thread (measured best of 8-24)
-constexpr int kRing = 32;         // list slots per lane staged in LDS
 
 __device__ __forceinline__ int wave_min_int(int v) {
 #pragma unroll
@@ -1599,8 +1598,6 @@ static __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 
 // ---- staged list build (large systems)
 
-constexpr int kStageCells = 1600;  // cells of a region at most
-constexpr int kStageTest = 4;      // candidates tested together
 constexpr int kStageLanes = 2;     // lanes per particle of the staged list build
 constexpr int kStageThreads = kStageSlots * kStageLanes;
 
@@ -1807,13 +1804,6 @@ __device__ __forceinline__ int stage_lists(const SysConst &c, const SysPtrs &p, 
   return count;
 }
 
-// Dynamic LDS of the staged list build: the region's positions, its cell starts and the
-// waves' entry rings.
-__host__ __device__ inline size_t stage_list_bytes(const SysConst &c) {
-  return sizeof(float4) * (size_t)(c.stage_cap + 1 + kStageTest) + sizeof(unsigned short) * (kStageCells + 8) +
-         sizeof(unsigned short) * kRing * kStageSlots;
-}
-
 // Verlet lists of large systems for units of kStageSlots sorted slots (slabs of a column
 // of the cell order).  The workgroup copies the region of cells around its slots into
 // LDS once (the cells' first places by a prefix sum over their counts) and each
@@ -1991,7 +1981,7 @@ static __global__ __launch_bounds__(kStageThreads) __attribute__((amdgpu_waves_p
     }
   } else {
     unsigned *cand = reinterpret_cast<unsigned *>(s_pos) + wv * kWaveCand;
-    const int fw = min(nw, (int)(stage_list_bytes(c) / (sizeof(unsigned) * kWaveCand)));  // waves whose windows fit
+    const int fw = min(nw, (int)(stage_list_bytes(c.stage_cap) / (sizeof(unsigned) * kWaveCand)));  // waves whose windows fit
     for (int q = s0 + wv; wv < fw && q < s1; q += fw) {
       const int k = list_wave_one<false>(c, p, cur, q, cand, s_cs2, p.t_pos, p.cell_start, longest);
       if (lane == 0) kept += k;
@@ -4017,9 +4007,7 @@ size_t big_lds_bytes() { return 4 * (size_t)(kPersistThreads / 64 * kWaveCand); 
 
 int stage_units(int n) { return (n + kStageSlots - 1) / kStageSlots; }
 
-size_t stage_list_lds(const SysConst &c) { return stage_list_bytes(c); }
-
-int stage_max_cells() { return kStageCells; }
+size_t stage_list_lds(const SysConst &c) { return stage_list_bytes(c.stage_cap); }
 
 bool stage_supported(int tp) { return staged_tp(tp); }
 

@@ -31,7 +31,6 @@ hipError_t launch_call_begin(hipStream_t st, const SysConst &c, const SysPtrs &p
                              int thermo_every, long long trace_cap,
                              long long nsteps);
 int stage_units(int n);
-int stage_max_cells();
 bool stage_supported(int tp);
 hipError_t launch_stage_expand(hipStream_t st, const SysConst &c, const SysPtrs &p, bool drop);
 hipError_t launch_arm(hipStream_t st, Control *ctl, int cur, long long nsteps);
@@ -456,30 +455,12 @@ srmd_status fill_const(srmd_system *s) {
     c.tile_mq1[k] = 65536 / (c.tile_q[k] + 1) + 1;
   }
   while ((1 << c.tp_shift) < s->tp) ++c.tp_shift;
-  // Staged lists (k_list_stage and the staged step and force kernels): large systems
-  // with the thread-per-particle list and blocks of whole units.  What a unit copies is
-  // its slab (about 5 x 5 cells and the layers that hold its slots) widened by the list
-  // radius, and a third more (over jittered lattices of 16 000 to 256 000 particles of
-  // both fluids no unit needed more than 1.15 times the estimate, nor did those that end
-  // one column and begin the next).  10 cells along every axis, so that
-  // a test without image arithmetic never sees a distance of half a box side.
-  if (!c.small_sort && c.list_kind == 2 && stage_supported(s->tp) && s->ppb % kStageSlots == 0 && c.nc[0] >= 10 &&
-      c.nc[1] >= 10 && c.nc[2] >= 10 && s->n < (1 << 28)) {
-    const double rho = s->n / V, a = c.tile_q[0] * c.Ld[0] / c.nc[0], b = c.tile_q[1] * c.Ld[1] / c.nc[1];
-    const double layers = kStageSlots / (rho * a * b) / (c.Ld[2] / c.nc[2]);
-    const double h = (layers + 0.6) * c.Ld[2] / c.nc[2];
-    const double region = rho * (a * b * h + 2.0 * reach * (a * b + b * h + a * h) + M_PI * reach * reach * (a + b + h) +
-                                 4.0 / 3.0 * M_PI * reach * reach * reach);
-    const double cells = (c.tile_q[0] + 4.0) * (c.tile_q[1] + 4.0) * (layers + 5.0);
-    const int units = s->ppb / kStageSlots;
-    // with one unit per block, what lets five blocks share a compute unit's LDS (32 000
-    // bytes with the static 2.4 KB) if that is still a fifth more than the estimate
-    int cap = std::max(1024, (int)(1.35 * region));
-    if (s->tp == 1 && units == 1 && 1.2 * region <= 1850) cap = std::min(cap, 1850);
-    if (units * (cap + 1) <= 9400 && 1.3 * cells <= stage_max_cells()) {
+  if (!c.small_sort && c.list_kind == 2 && stage_supported(s->tp)) {
+    const StagePlan plan = stage_plan(s->n, c.Ld, c.nc, c.tile_q, reach, s->tp, s->ppb);
+    if (plan.cap > 0) {
       c.stage = 1;
-      c.stage_cap = cap;
-      c.stage_lds = units * (cap + 1);
+      c.stage_cap = plan.cap;
+      c.stage_lds = plan.lds;
       c.stage_reach2 = (float)(reach * reach * (1.0 + 1e-3));
     }
   }

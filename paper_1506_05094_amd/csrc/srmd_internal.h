@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "plans.h"
+
 namespace srmd {
 
 constexpr int kMaxTypes = 4;
@@ -19,8 +21,6 @@ __host__ __device__ inline int scan_tile_shift(int ncell) {
   return s;
 }
 __host__ __device__ inline int scan_tiles(int ncell) { return ((ncell - 1) >> scan_tile_shift(ncell)) + 1; }
-
-constexpr int kStageSlots = 256;  // sorted slots of a unit of the staged lists
 
 // Per-type-pair float32 constants of the pair kernel and of the list build.
 struct PairTable {
