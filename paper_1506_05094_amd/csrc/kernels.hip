@@ -452,6 +452,27 @@ __device__ __forceinline__ void lj_pair(const float4 pi, const Wide &wi, const f
   w = __builtin_fmaf(fr, r2, w);
 }
 
+// The selects of lj_pair leave a pair out of range a product with 0, which a non-finite
+// coordinate (of the neighbour, or the particle's own in an idle slot) turns into NaN; such
+// a pair contributes nothing (no distance to it is below a cutoff).  So a lane whose sums are
+// not finite takes its mine entries again one by one and leaves those out: the same sums
+// unless a pair in range is itself not finite.  entry(m): the lane's entry m.
+template <int METHOD, class Entry>
+__device__ __forceinline__ void finite_sums(const float4 pi, int mine, Entry entry, const SharedPairs &sp,
+                                            const SysConst &c, float &fx, float &fy, float &fz, float &u, float &w) {
+  if (fabsf((fx + fy) + (fz + w)) < __builtin_inff()) return;
+  const int row0 = ptype(pi) * c.ntypes;
+  const Wide wi = widen(pi);
+  fx = fy = fz = u = w = 0.f;
+#pragma unroll 1
+  for (int m = 0; m < mine; ++m) {
+    const float4 q = entry(m);
+    float dx, dy, dz;
+    if (dist2(pi, q, c, dx, dy, dz) < __builtin_inff())
+      lj_pair<METHOD, true, false>(pi, wi, q, true, row0, sp, c, fx, fy, fz, u, w);
+  }
+}
+
 // Pairs evaluated together: a group is skipped (uniformly) once every lane's list has
 // ended.  1, 2 and 4 measured within 1 % of each other; with whole batches of 8 a wave
 // of lists of 10 entries did 16 pairs of work.
@@ -686,6 +707,9 @@ __device__ __forceinline__ void force_lane(int i, int t, bool active, const floa
   } else {
     force_loop<TP, METHOD, B, true, false>(i, pi, pos, row, stride, mine, wmax, j, sp, c, fx, fy, fz, u, w);
   }
+  if constexpr (METHOD <= 3)
+    finite_sums<METHOD>(
+        pi, mine, [&](int m) { return pos[*(row + (long long)m * stride + lane)]; }, sp, c, fx, fy, fz, u, w);
 }
 
 // Least of the lanes' values (at most 1e30), uniform.
@@ -819,6 +843,14 @@ __device__ __forceinline__ void force_lane_staged(int i, int t, bool active, con
   } else {
     stage_loop<TP, METHOD, true, false>(pi, region, row, stride, col, mine, words, j, sp, c, fx, fy, fz, u, w);
   }
+  if constexpr (METHOD <= 3)
+    finite_sums<METHOD>(
+        pi, mine,
+        [&](int m) {
+          const unsigned two = row[(long long)(m >> 1) * stride + col];
+          return region[m & 1 ? two >> 16 : two & 0xffffu];
+        },
+        sp, c, fx, fy, fz, u, w);
 }
 
 // Inclusive prefix sum over the lanes of a wave, exact for integers: within each row
