@@ -402,6 +402,10 @@ void resolve_persistent(srmd_system *s) {
     s->persist_groups = want;
 }
 
+// The automatic builder without staged lists: measured on MI355X (LJ fluid) the cell builder
+// is the fastest from 16k to 64k particles, the thread builder from 256k on.
+bool auto_cell_builder(const srmd_system *s) { return s->list_mode == 0 && s->n > 4096 && s->n <= 131072; }
+
 // The kernel constants of s: launch shape, cell grid, list capacity and the
 // per-type-pair tables (host only; no device memory is touched).
 srmd_status fill_const(srmd_system *s) {
@@ -437,10 +441,8 @@ srmd_status fill_const(srmd_system *s) {
   c.volume = V;
   const bool fits = small_sort_fits(s->n, c.ncell);
   c.small_sort = (s->sort_mode == 0 || s->sort_mode == 1) && fits ? 1 : 0;
-  // measured on MI355X (LJ fluid): without staged lists the cell builder is fastest from
-  // 16k to 64k particles and the thread builder from 256k on; the staged form of the
-  // thread builder (below) is the fastest wherever it applies; the autotuner compares all
-  const bool auto_cell = s->list_mode == 0 && s->n > 4096 && s->n <= 131072;
+  // measured on MI355X (LJ fluid): the staged form of the thread builder (below) is the
+  // fastest wherever it applies; the autotuner compares all
   c.list_kind = s->list_mode != 0 ? s->list_mode : s->n <= 4096 ? 1 : c.small_sort ? 3 : 2;
   if (c.list_kind == 4 && !c.small_sort)
     return fail(s, SRMD_EINVAL, "the all-pairs list build takes systems of at most 8192 particles and 8192 cells "
@@ -464,7 +466,7 @@ srmd_status fill_const(srmd_system *s) {
       c.stage_reach2 = (float)(reach * reach * (1.0 + 1e-3));
     }
   }
-  if (auto_cell && !c.stage) c.list_kind = 3;
+  if (!c.stage && auto_cell_builder(s)) c.list_kind = 3;
   c.list_blocks = std::max(1, std::min((s->n + 255) / 256, 2048));
   c.pot_kind = s->pot >= 2 ? s->pot : 0;
   c.sort_every = c.list_kind == 4 ? s->sort_every : 0;
@@ -613,6 +615,7 @@ srmd_status prepare(srmd_system *s) {
       s->list16_alloc = 0;
       s->stage_alloc = 0;
       c.stage = 0;
+      if (auto_cell_builder(s)) c.list_kind = 3;
       (void)hipGetLastError();
     }
   }

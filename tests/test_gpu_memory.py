@@ -1,0 +1,88 @@
+"""Refused device memory: what a system does without its optional arrays."""
+import contextlib
+
+import numpy as np
+import pytest
+
+from workloads import generators as gen
+
+from gpu_common import make_system
+
+pytestmark = pytest.mark.gpu
+
+N = 20011
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1506_05094_amd import srmd
+    srmd.load()
+
+
+class Hook:
+    """Allocations through torch; refuse(sizes so far, bytes) says which fail."""
+
+    def __init__(self):
+        self.sizes, self.live, self.refused, self.refuse = [], {}, [], lambda sizes, nbytes: False
+
+    def alloc(self, nbytes, ctx):
+        import torch
+        nbytes = int(nbytes)
+        if self.refuse(self.sizes, nbytes):
+            self.refused.append(nbytes)
+            return None
+        self.sizes.append(nbytes)
+        t = torch.empty(max(nbytes, 1), dtype=torch.uint8, device="cuda")
+        self.live[t.data_ptr()] = t
+        return t.data_ptr()
+
+    def free(self, ptr, ctx):
+        self.live.pop(int(ptr), None)
+
+    def held(self):
+        return sum(t.numel() for t in self.live.values())
+
+
+@contextlib.contextmanager
+def hooked():
+    from paper_1506_05094_amd import srmd
+    h = Hook()
+    a, f = srmd._ALLOC_T(h.alloc), srmd._FREE_T(h.free)
+    srmd._check(srmd.load().srmd_set_allocator(a, f, None))
+    try:
+        yield h
+    finally:
+        srmd.uninstall_allocator()
+
+
+def _state(n=N):
+    return gen.jitter_positions(gen.lj_fcc_state(n, gen.LJ_RHO, gen.LJ_T, n), 0.08, 3)
+
+
+def _liquid(state, launch=(1, 256), list_mode=0, precision="f32"):
+    s = make_system(state, *gen.lj_params(), "sp", launch=launch, precision=precision)
+    s.set_rebuild_path(0, list_mode)
+    s.set_integrator_nve(0.004)
+    return s
+
+
+def test_automatic_builder_without_the_staged_arrays():
+    """Where the staged lists' arrays are refused, the automatic choice is that of a system
+    without staged lists: the cell builder up to 131072 particles."""
+    print("automatic builder, staged arrays refused", flush=True)
+    with _liquid(_state()) as s:
+        s.step(20)
+        want, stats = s.get_state(), s.stats()
+        plain = 4 * stats["n_max"] * ((N + 63) // 64 * 64)
+    assert stats["list_mode"] == 2
+    with hooked() as h:
+        h.refuse = lambda sizes, nbytes: plain in sizes and 2 * nbytes == plain  # the 16-bit lists
+        with _liquid(_state()) as s:
+            s.step(20)
+            got, stats = s.get_state(), s.stats()
+    assert h.refused and stats["list_mode"] == 3
+    for k in ("pos", "vel", "force", "image"):
+        np.testing.assert_array_equal(got[k], want[k], err_msg=k)
