@@ -185,7 +185,10 @@ DevBuf raw_alloc(size_t bytes) {
   if (g_alloc.alloc) {
     b.ptr = g_alloc.alloc(bytes, g_alloc.ctx);
   } else {
-    if (hipMalloc(&b.ptr, bytes) != hipSuccess) b.ptr = nullptr;
+    if (hipMalloc(&b.ptr, bytes) != hipSuccess) {
+      b.ptr = nullptr;
+      (void)hipGetLastError();  // a refusal is handled here, not by the next launch's check
+    }
   }
   return b;
 }
@@ -566,6 +569,8 @@ srmd_status prepare(srmd_system *s) {
   const long long need_nbl = (long long)nmax * c.nvp;
   if (need_nbl > s->nbl_alloc) {
     dev_free(s, s->p.nbl);
+    s->nbl_alloc = 0;
+    s->p.nbl = nullptr;
     s->p.nbl = (int *)dev_alloc(s, sizeof(int) * (size_t)need_nbl);
     if (!s->p.nbl) return fail(s, SRMD_ENOMEM, "neighbour list allocation failed");
     s->nbl_alloc = need_nbl;
@@ -573,6 +578,7 @@ srmd_status prepare(srmd_system *s) {
   if (c.ncell + 1 > s->ncell_alloc) {
     dev_free(s, s->p.cell_count);
     dev_free(s, s->p.cell_start);
+    s->ncell_alloc = 0;
     s->p.cell_count = (unsigned *)dev_alloc(s, sizeof(unsigned) * (size_t)(c.ncell + 1));
     s->p.cell_start = (unsigned *)dev_alloc(s, sizeof(unsigned) * (size_t)(c.ncell + 1));
     if (!s->p.cell_count || !s->p.cell_start) return fail(s, SRMD_ENOMEM, "cell arrays allocation failed");
@@ -587,6 +593,7 @@ srmd_status prepare(srmd_system *s) {
   const int nparts = 2 * blocks + blocks * (threads / 64);
   if (nparts > s->part_alloc) {
     dev_free(s, s->p.part);
+    s->part_alloc = 0;
     s->p.part = (BlockPartial *)dev_alloc(s, sizeof(BlockPartial) * (size_t)nparts);
     if (!s->p.part) return fail(s, SRMD_ENOMEM, "partials allocation failed");
     s->part_alloc = nparts;
@@ -1056,14 +1063,15 @@ srmd_status restore_host_state(srmd_system *s, const HostState &h) {
 
 srmd_status ensure_trace(srmd_system *s, long long cap) {
   if (cap <= s->trace_alloc) return SRMD_OK;
-  dev_free(s, s->p.trace);
-  s->p.trace = (Thermo *)dev_alloc(s, sizeof(Thermo) * (size_t)cap);
-  if (!s->p.trace) return fail(s, SRMD_ENOMEM, "trace allocation failed");
-  s->trace_alloc = cap;
   // the pointer is baked into the captured graphs (the persistent and batch
   // descriptors are compared with the system before every launch); the list and
   // the trajectory do not depend on the trace, so no rebuild is requested
   drop_graphs(s);
+  dev_free(s, s->p.trace);
+  s->trace_alloc = 0;
+  s->p.trace = (Thermo *)dev_alloc(s, sizeof(Thermo) * (size_t)cap);
+  if (!s->p.trace) return fail(s, SRMD_ENOMEM, "trace allocation failed");
+  s->trace_alloc = cap;
   return SRMD_OK;
 }
 

@@ -86,3 +86,16 @@ def test_automatic_builder_without_the_staged_arrays():
     assert h.refused and stats["list_mode"] == 3
     for k in ("pos", "vel", "force", "image"):
         np.testing.assert_array_equal(got[k], want[k], err_msg=k)
+
+
+def test_a_smaller_trace_after_a_refused_one():
+    """A trace buffer that could not grow leaves none behind: the next call makes its own."""
+    from paper_1506_05094_amd import srmd
+    print("refused trace", flush=True)
+    with hooked() as h, _liquid(_state(), list_mode=1) as s:
+        s.step(8, thermo_every=1)
+        h.refuse = lambda sizes, nbytes: nbytes > 10 * 1024
+        with pytest.raises(srmd.SrmdError) as e:
+            s.step(1000, thermo_every=1)
+        assert e.value.status == srmd.SRMD_ENOMEM
+        assert len(s.step(4, thermo_every=1)) == 4 and s.stats()["steps"] == 12
