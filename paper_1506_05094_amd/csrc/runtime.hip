@@ -138,6 +138,7 @@ struct srmd_system {
   long long trace_alloc = 0;
   long long list16_alloc = 0;
   size_t stage_alloc = 0;
+  bool no_stage = false;  // memory was refused: plain lists from then on
   int part_alloc = 0;
   std::vector<DevBuf> bufs;
   // snapshot for list-overflow replay
@@ -224,6 +225,46 @@ void dev_free(srmd_system *s, void *ptr) {
 void drop_graphs(srmd_system *s) {
   for (auto &kv : s->graphs) (void)hipGraphExecDestroy(kv.second);
   s->graphs.clear();
+}
+
+// The automatic builder without staged lists: measured on MI355X (LJ fluid) the cell builder
+// is the fastest from 16k to 64k particles, the thread builder from 256k on.
+bool auto_cell_builder(const srmd_system *s) { return s->list_mode == 0 && s->n > 4096 && s->n <= 131072; }
+
+// Plain lists from now on.
+void unstage(srmd_system *s) {
+  s->no_stage = true;
+  if (s->c.stage && auto_cell_builder(s)) s->c.list_kind = 3;
+  s->c.stage = 0;
+  drop_graphs(s);  // they hold the constants and the pointers
+}
+
+// Give back the device memory that the system can do without: the buffer of state transfers
+// and the staged lists' arrays, whose lists become plain ones (the same entries in the same
+// order) for the rest of the system's life.  Returns whether there was any.
+bool give_back(srmd_system *s) {
+  if (!s->d_xfer && !s->p.list16 && !s->p.stage_src && !s->p.stage_n) return false;
+  if (s->c.stage && !s->dirty && s->p.nbl) (void)launch_stage_expand(s->stream, s->c, s->p, true);
+  (void)hipStreamSynchronize(s->stream);
+  dev_free(s, s->d_xfer);
+  s->d_xfer = nullptr;
+  if (s->p.list16 || s->p.stage_src || s->p.stage_n) {
+    dev_free(s, s->p.list16);
+    dev_free(s, s->p.stage_src);
+    dev_free(s, s->p.stage_n);
+    s->p.list16 = s->p.stage_src = nullptr;
+    s->p.stage_n = nullptr;
+    s->list16_alloc = 0;
+    s->stage_alloc = 0;
+    unstage(s);
+  }
+  return true;
+}
+
+// dev_alloc for what the system needs: before a refusal counts, the rest is given back.
+void *need_alloc(srmd_system *s, size_t bytes) {
+  void *q = dev_alloc(s, bytes);
+  return q || !give_back(s) ? q : dev_alloc(s, bytes);
 }
 
 int pair_index(const srmd_system *s, int a, int b) { return a * s->ntypes + b; }
@@ -405,10 +446,6 @@ void resolve_persistent(srmd_system *s) {
     s->persist_groups = want;
 }
 
-// The automatic builder without staged lists: measured on MI355X (LJ fluid) the cell builder
-// is the fastest from 16k to 64k particles, the thread builder from 256k on.
-bool auto_cell_builder(const srmd_system *s) { return s->list_mode == 0 && s->n > 4096 && s->n <= 131072; }
-
 // The kernel constants of s: launch shape, cell grid, list capacity and the
 // per-type-pair tables (host only; no device memory is touched).
 srmd_status fill_const(srmd_system *s) {
@@ -460,7 +497,7 @@ srmd_status fill_const(srmd_system *s) {
     c.tile_mq1[k] = 65536 / (c.tile_q[k] + 1) + 1;
   }
   while ((1 << c.tp_shift) < s->tp) ++c.tp_shift;
-  if (!c.small_sort && c.list_kind == 2 && stage_supported(s->tp)) {
+  if (!c.small_sort && c.list_kind == 2 && stage_supported(s->tp) && !s->no_stage) {
     const StagePlan plan = stage_plan(s->n, c.Ld, c.nc, c.tile_q, reach, s->tp, s->ppb);
     if (plan.cap > 0) {
       c.stage = 1;
@@ -571,7 +608,7 @@ srmd_status prepare(srmd_system *s) {
     dev_free(s, s->p.nbl);
     s->nbl_alloc = 0;
     s->p.nbl = nullptr;
-    s->p.nbl = (int *)dev_alloc(s, sizeof(int) * (size_t)need_nbl);
+    s->p.nbl = (int *)need_alloc(s, sizeof(int) * (size_t)need_nbl);
     if (!s->p.nbl) return fail(s, SRMD_ENOMEM, "neighbour list allocation failed");
     s->nbl_alloc = need_nbl;
   }
@@ -579,8 +616,8 @@ srmd_status prepare(srmd_system *s) {
     dev_free(s, s->p.cell_count);
     dev_free(s, s->p.cell_start);
     s->ncell_alloc = 0;
-    s->p.cell_count = (unsigned *)dev_alloc(s, sizeof(unsigned) * (size_t)(c.ncell + 1));
-    s->p.cell_start = (unsigned *)dev_alloc(s, sizeof(unsigned) * (size_t)(c.ncell + 1));
+    s->p.cell_count = (unsigned *)need_alloc(s, sizeof(unsigned) * (size_t)(c.ncell + 1));
+    s->p.cell_start = (unsigned *)need_alloc(s, sizeof(unsigned) * (size_t)(c.ncell + 1));
     if (!s->p.cell_count || !s->p.cell_start) return fail(s, SRMD_ENOMEM, "cell arrays allocation failed");
     HIPCHK(s, hipMemsetAsync(s->p.cell_count, 0, sizeof(unsigned) * (size_t)(c.ncell + 1), s->stream));
     HIPCHK(s, hipMemsetAsync(s->p.cell_start, 0, sizeof(unsigned) * (size_t)(c.ncell + 1), s->stream));
@@ -594,7 +631,7 @@ srmd_status prepare(srmd_system *s) {
   if (nparts > s->part_alloc) {
     dev_free(s, s->p.part);
     s->part_alloc = 0;
-    s->p.part = (BlockPartial *)dev_alloc(s, sizeof(BlockPartial) * (size_t)nparts);
+    s->p.part = (BlockPartial *)need_alloc(s, sizeof(BlockPartial) * (size_t)nparts);
     if (!s->p.part) return fail(s, SRMD_ENOMEM, "partials allocation failed");
     s->part_alloc = nparts;
   }
@@ -614,16 +651,8 @@ srmd_status prepare(srmd_system *s) {
     if (s->p.list16 && s->p.stage_src && s->p.stage_n) {
       HIPCHK(s, hipMemsetAsync(s->p.stage_n, 0, sizeof(int) * units, s->stream));
     } else {  // no memory beside the plain lists (which bound the system's size): use those
-      dev_free(s, s->p.list16);
-      dev_free(s, s->p.stage_src);
-      dev_free(s, s->p.stage_n);
-      s->p.list16 = s->p.stage_src = nullptr;
-      s->p.stage_n = nullptr;
-      s->list16_alloc = 0;
-      s->stage_alloc = 0;
-      c.stage = 0;
-      if (auto_cell_builder(s)) c.list_kind = 3;
-      (void)hipGetLastError();
+      give_back(s);
+      unstage(s);
     }
   }
   resolve_persistent(s);
@@ -713,13 +742,13 @@ srmd_status alloc_snapshot(srmd_system *s) {
   if (s->snap.pos) return SRMD_OK;
   const size_t n = (size_t)s->n;
   Snapshot &q = s->snap;
-  q.pos = (float4 *)dev_alloc(s, sizeof(float4) * n);
-  q.vel = (float4 *)dev_alloc(s, sizeof(float4) * n);
-  q.last = (float4 *)dev_alloc(s, sizeof(float4) * n);
-  q.img = (int4 *)dev_alloc(s, sizeof(int4) * n);
-  q.ctl = (Control *)dev_alloc(s, sizeof(Control));
-  if (s->prec == SRMD_PREC_F64POS) q.pos64 = (double *)dev_alloc(s, sizeof(double) * 3 * n);
-  if (s->prec == SRMD_PREC_F32_KAHAN) q.kahan = (float4 *)dev_alloc(s, sizeof(float4) * n);
+  q.pos = (float4 *)need_alloc(s, sizeof(float4) * n);
+  q.vel = (float4 *)need_alloc(s, sizeof(float4) * n);
+  q.last = (float4 *)need_alloc(s, sizeof(float4) * n);
+  q.img = (int4 *)need_alloc(s, sizeof(int4) * n);
+  q.ctl = (Control *)need_alloc(s, sizeof(Control));
+  if (s->prec == SRMD_PREC_F64POS) q.pos64 = (double *)need_alloc(s, sizeof(double) * 3 * n);
+  if (s->prec == SRMD_PREC_F32_KAHAN) q.kahan = (float4 *)need_alloc(s, sizeof(float4) * n);
   if (!q.pos || !q.vel || !q.last || !q.img || !q.ctl || (s->p.pos64 && !q.pos64) || (s->p.kahan && !q.kahan)) {
     for (void *b : {(void *)q.pos, (void *)q.vel, (void *)q.last, (void *)q.img, (void *)q.ctl, (void *)q.pos64,
                     (void *)q.kahan})
@@ -797,8 +826,8 @@ srmd_status launch_persistent(srmd_system *s, int cnt) {
   if (g > s->jobs_cap) {
     dev_free(s, s->d_jobs);
     dev_free(s, s->d_job_off);
-    s->d_jobs = (CoopJob *)dev_alloc(s, sizeof(CoopJob) * (size_t)g);
-    s->d_job_off = (int *)dev_alloc(s, sizeof(int) * (size_t)(g + 1));
+    s->d_jobs = (CoopJob *)need_alloc(s, sizeof(CoopJob) * (size_t)g);
+    s->d_job_off = (int *)need_alloc(s, sizeof(int) * (size_t)(g + 1));
     if (!s->d_jobs || !s->d_job_off) return fail(s, SRMD_ENOMEM, "persistent job table allocation failed");
     s->jobs_cap = g;
     s->jobs_g = 0;
@@ -814,7 +843,7 @@ srmd_status launch_persistent(srmd_system *s, int cnt) {
     s->jobs_g = g;
   }
   if (!s->d_desc) {
-    s->d_desc = (ReplicaDesc *)dev_alloc(s, sizeof(ReplicaDesc));
+    s->d_desc = (ReplicaDesc *)need_alloc(s, sizeof(ReplicaDesc));
     if (!s->d_desc) return fail(s, SRMD_ENOMEM, "persistent descriptor allocation failed");
     s->desc_valid = false;
   }
@@ -1069,7 +1098,7 @@ srmd_status ensure_trace(srmd_system *s, long long cap) {
   drop_graphs(s);
   dev_free(s, s->p.trace);
   s->trace_alloc = 0;
-  s->p.trace = (Thermo *)dev_alloc(s, sizeof(Thermo) * (size_t)cap);
+  s->p.trace = (Thermo *)need_alloc(s, sizeof(Thermo) * (size_t)cap);
   if (!s->p.trace) return fail(s, SRMD_ENOMEM, "trace allocation failed");
   s->trace_alloc = cap;
   return SRMD_OK;

@@ -88,6 +88,48 @@ def test_automatic_builder_without_the_staged_arrays():
         np.testing.assert_array_equal(got[k], want[k], err_msg=k)
 
 
+def _uneven():
+    """The liquid in the lower half of a box twice as high: its lists outgrow the first capacity."""
+    st = _state()
+    box = st.box * np.array([1.0, 1.0, 2.0])
+    pos = st.pos.copy()
+    pos[:, 2] -= np.float32(st.box[2] / 2)
+    return gen.State(pos=gen._wrap_f32(pos, box), vel=st.vel, types=st.types, box=box, mass=st.mass, ntypes=1, seed=st.seed,
+                     recipe=st.recipe)
+
+
+def _run(state, list_mode, precision, h):
+    """Two calls, the second with records; what the system then holds, and the results."""
+    with _liquid(state, list_mode=list_mode, precision=precision) as s:
+        s.step(15)
+        trace = s.step(20, thermo_every=1)
+        held = h.held()
+        h.refuse = lambda sizes, nbytes: False
+        return held, (trace, s.get_state(), s.neighbor_pairs(), s.stats()["n_max"])
+
+
+@pytest.mark.parametrize("just_short", [False, True])
+@pytest.mark.parametrize("name,state,precision", [("even", _state, "f32"), ("uneven", _uneven, "f32"),
+                                                  ("f64pos", _state, "f64pos")])
+def test_steps_in_less_memory(name, state, precision, just_short):
+    """Under a budget of what the wave builder's plain lists hold in the end (arrays, snapshot,
+    trace, a list that grew), and of one byte less than staged lists do: they give their
+    arrays back instead of failing the call, on the same trajectory."""
+    print(f"memory: {name}, just short of the staged lists' {just_short}", flush=True)
+    with hooked() as h:
+        budget, want = _run(state(), 1, precision, h)
+        if just_short:
+            budget = _run(state(), 2, precision, h)[0] - 1
+    with hooked() as h:
+        h.refuse = lambda sizes, nbytes: h.held() + nbytes > budget
+        held, got = _run(state(), 2, precision, h)
+        assert h.refused and held <= budget
+    assert got[0].tobytes() == want[0].tobytes() and got[3] == want[3]
+    np.testing.assert_array_equal(got[2], want[2])
+    for k in ("pos", "vel", "force", "image", "pos64"):
+        np.testing.assert_array_equal(got[1][k], want[1][k], err_msg=k)
+
+
 def test_a_smaller_trace_after_a_refused_one():
     """A trace buffer that could not grow leaves none behind: the next call makes its own."""
     from paper_1506_05094_amd import srmd
