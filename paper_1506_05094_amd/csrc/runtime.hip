@@ -151,7 +151,7 @@ struct srmd_system {
     int bad, pad[3];
   } *h = nullptr;
   size_t h_xfer = 0;        // bytes of a state transfer that fit behind it (0: larger systems)
-  char *d_xfer = nullptr;   // device copy of a state in original order (state_bytes_xfer)
+  char *d_xfer = nullptr;   // device copy of a state in original order (xfer_bytes)
   std::map<std::pair<int, int>, hipGraphExec_t> graphs;
   int ahead_slots = kAheadSlots[0];  // run-ahead chains: steps after a rebuild slot
   long long ahead_step = -1, ahead_builds = 0;  // steps and list builds at the last reading (-1: none yet)
@@ -985,13 +985,82 @@ constexpr size_t kXferHead = 16;
 constexpr size_t kXferPinned = (size_t)1 << 23;
 size_t xfer_bytes(size_t n) { return kXferHead + 72 * n; }
 
-// The device buffer of state transfers, made at the first one.
-srmd_status ensure_xfer(srmd_system *s) {
-  if (s->d_xfer) return SRMD_OK;
+// A buffer above this size (3.7 million particles) is given back after each transfer: the
+// transfer takes tens of milliseconds then, beside which making it does not count.
+constexpr size_t kXferKeep = (size_t)1 << 28;
+
+// The device buffer of state transfers, made at the first one.  False: there is no memory
+// for it, and the host permutes (host_get_state, host_set_state).
+bool ensure_xfer(srmd_system *s) {
+  if (s->d_xfer) return true;
   s->d_xfer = (char *)dev_alloc(s, xfer_bytes((size_t)s->n));
-  if (!s->d_xfer) return fail(s, SRMD_ENOMEM, "state transfer buffer allocation failed");
-  HIPCHK(s, hipMemsetAsync(s->d_xfer, 0, kXferHead, s->stream));  // the status word is only ever set
+  if (!s->d_xfer) return false;
+  // the status word is only ever set
+  if (hipMemsetAsync(s->d_xfer, 0, kXferHead, s->stream) == hipSuccess) return true;
+  dev_free(s, s->d_xfer);
+  s->d_xfer = nullptr;
+  return false;
+}
+
+// After a transfer, with the stream drained.
+void release_xfer(srmd_system *s) {
+  if (!s->d_xfer || xfer_bytes((size_t)s->n) <= kXferKeep) return;
+  dev_free(s, s->d_xfer);
+  s->d_xfer = nullptr;
+}
+
+// srmd_get_state with no device memory beside the system's own: the slots' arrays to the
+// host, permuted there.
+srmd_status host_get_state(srmd_system *s, float *pos, float *vel, int32_t *image, float *force, double *pos64) {
+  const size_t n = (size_t)s->n;
+  std::vector<int4> hi(n);
+  std::vector<float4> hp(n), hv(vel ? n : 0), hf(force ? n : 0);
+  std::vector<double> h64(pos64 && s->p.pos64 ? 3 * n : 0);
+  auto down = [&](void *to, const void *from, size_t bytes) {
+    return bytes ? hipMemcpyAsync(to, from, bytes, hipMemcpyDeviceToHost, s->stream) : hipSuccess;
+  };
+  HIPCHK(s, down(hi.data(), s->p.img, sizeof(int4) * n));
+  HIPCHK(s, down(hp.data(), s->p.pos[s->cur], sizeof(float4) * n));
+  HIPCHK(s, down(hv.data(), s->p.vel, sizeof(float4) * hv.size()));
+  HIPCHK(s, down(hf.data(), s->p.force, sizeof(float4) * hf.size()));
+  HIPCHK(s, down(h64.data(), s->p.pos64, sizeof(double) * h64.size()));
+  HIPCHK(s, hipStreamSynchronize(s->stream));
+  for (size_t k = 0; k < n; ++k)
+    if (hi[k].w < 0 || (size_t)hi[k].w >= n) return fail(s, SRMD_ESTATE, "corrupt particle id on the device");
+  for (size_t k = 0; k < n; ++k) {
+    const size_t d = 3 * (size_t)hi[k].w;
+    for (size_t e = 0; e < 3; ++e) {
+      if (pos) pos[d + e] = (&hp[k].x)[e];
+      if (vel) vel[d + e] = (&hv[k].x)[e];
+      if (image) image[d + e] = (&hi[k].x)[e];
+      if (force) force[d + e] = (&hf[k].x)[e];
+      if (pos64) pos64[d + e] = h64.empty() ? (double)(&hp[k].x)[e] : h64[3 * k + e];
+    }
+  }
   return SRMD_OK;
+}
+
+srmd_status upload_state(srmd_system *s, const float *pos, const float *vel, const int32_t *type);
+
+// srmd_set_state with no device memory beside the system's own: the current state to the
+// host, the new one up from there.
+srmd_status host_set_state(srmd_system *s, const float *pos, const float *vel) {
+  const size_t n = (size_t)s->n;
+  std::vector<float> P(3 * n), V(3 * n);
+  srmd_status st = host_get_state(s, P.data(), V.data(), nullptr, nullptr, nullptr);
+  if (st != SRMD_OK) return st;
+  std::vector<int4> hi(n);
+  std::vector<float4> hp(n);
+  HIPCHK(s, hipMemcpyAsync(hi.data(), s->p.img, sizeof(int4) * n, hipMemcpyDeviceToHost, s->stream));
+  HIPCHK(s, hipMemcpyAsync(hp.data(), s->p.pos[s->cur], sizeof(float4) * n, hipMemcpyDeviceToHost, s->stream));
+  HIPCHK(s, hipStreamSynchronize(s->stream));
+  std::vector<int32_t> type(n);
+  for (size_t k = 0; k < n; ++k) std::memcpy(&type[(size_t)hi[k].w], &hp[k].w, sizeof(int32_t));
+  st = upload_state(s, pos ? pos : P.data(), vel ? vel : V.data(), type.data());
+  if (st != SRMD_OK) return st;
+  st = set_ctl_int(s, offsetof(Control, error), 0);  // errors of the replaced state do not carry over
+  if (st != SRMD_OK) return st;
+  return request_rebuild(s);
 }
 
 bool all_finite(const float *x, size_t count) {
@@ -1422,7 +1491,14 @@ srmd_status srmd_create(srmd_system **out, int32_t n, int32_t ntypes, const doub
     s->own_stream = true;
   }
   if (xfer_bytes((size_t)n) <= kXferPinned) s->h_xfer = xfer_bytes((size_t)n);
-  if (hipHostMalloc((void **)&s->h, sizeof(*s->h) + s->h_xfer, hipHostMallocDefault) != hipSuccess) {
+  bool pinned = hipHostMalloc((void **)&s->h, sizeof(*s->h) + s->h_xfer, hipHostMallocDefault) == hipSuccess;
+  if (!pinned && s->h_xfer > 0) {  // state transfers do without their part of it
+    (void)hipGetLastError();
+    s->h_xfer = 0;
+    pinned = hipHostMalloc((void **)&s->h, sizeof(*s->h), hipHostMallocDefault) == hipSuccess;
+  }
+  if (!pinned) {
+    (void)hipGetLastError();
     s->h = nullptr;
     srmd_destroy(s);
     return fail(nullptr, SRMD_ENOMEM, "pinned host allocation failed");
@@ -1800,8 +1876,7 @@ srmd_status srmd_step(srmd_system *s, int64_t nsteps, int32_t thermo_every, srmd
 
 srmd_status srmd_get_state(srmd_system *s, float *pos, float *vel, int32_t *image, float *force, double *pos64) {
   if (!s) return fail(nullptr, SRMD_EINVAL, "system is NULL");
-  srmd_status st = ensure_xfer(s);
-  if (st != SRMD_OK) return st;
+  if (!ensure_xfer(s)) return host_get_state(s, pos, vel, image, force, pos64);
   const size_t n = (size_t)s->n, vec = 12 * n;
   char *const base = s->d_xfer + kXferHead;
   StateXfer o{};
@@ -1835,9 +1910,10 @@ srmd_status srmd_get_state(srmd_system *s, float *pos, float *vel, int32_t *imag
   }
   if (s->h->bad) {
     const int zero = 0;
-    st = h2d_sync(s, s->d_xfer, &zero, sizeof(int));
+    const srmd_status st = h2d_sync(s, s->d_xfer, &zero, sizeof(int));
     return st != SRMD_OK ? st : fail(s, SRMD_ESTATE, "corrupt particle id on the device");
   }
+  release_xfer(s);
   return SRMD_OK;
 }
 
@@ -1865,8 +1941,7 @@ srmd_status srmd_set_state(srmd_system *s, const float *pos, const float *vel) {
   const size_t n = (size_t)s->n, vec = 12 * n;
   if (pos && !all_finite(pos, 3 * n)) return fail(s, SRMD_EINVAL, "non-finite position");
   if (vel && !all_finite(vel, 3 * n)) return fail(s, SRMD_EINVAL, "non-finite velocity");
-  srmd_status st = ensure_xfer(s);
-  if (st != SRMD_OK) return st;
+  if (!ensure_xfer(s)) return host_set_state(s, pos, vel);
   StateXfer in{};
   auto up = [&](const float *from, size_t off) -> float * {
     float *q = (float *)(s->d_xfer + kXferHead + off);
@@ -1878,6 +1953,7 @@ srmd_status srmd_set_state(srmd_system *s, const float *pos, const float *vel) {
   HIPCHK(s, launch_state_in(s->stream, s->p, s->n, s->cur, s->Lf, in));
   s->sort_pending = true;
   HIPCHK(s, hipStreamSynchronize(s->stream));  // the caller's arrays are read during the call only
+  release_xfer(s);
   return SRMD_OK;
 }
 

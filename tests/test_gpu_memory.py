@@ -141,3 +141,49 @@ def test_a_smaller_trace_after_a_refused_one():
             s.step(1000, thermo_every=1)
         assert e.value.status == srmd.SRMD_ENOMEM
         assert len(s.step(4, thermo_every=1)) == 4 and s.stats()["steps"] == 12
+
+
+@pytest.mark.parametrize("n,precision", [(700, "f32"), (700, "f64pos"), (9001, "f32_kahan"), (9001, "f64pos"), (130001, "f32")])
+def test_state_transfers_without_device_memory(n, precision):
+    """With every further allocation refused, states are read and set as with the transfer
+    buffer, a new state with and without positions or velocities."""
+    print(f"state transfers, no device memory: {n} {precision}", flush=True)
+    state = _state(n)
+    rng = np.random.default_rng(n)
+    pos = (state.pos + 3.0 * rng.standard_normal((n, 3))).astype(np.float32)  # past the faces: wrapped
+    vel = rng.standard_normal((n, 3)).astype(np.float32)
+    out = []
+    for refused in (False, True):
+        with hooked() as h, _liquid(state, launch=(1, 64), list_mode=1, precision=precision) as s:
+            s.step(5)
+            h.refuse = lambda sizes, nbytes: refused
+            seen = [s.get_state()]
+            for new in (dict(vel=vel), dict(pos=state.pos), dict(pos=pos, vel=vel)):
+                s.set_state(**new)
+                seen.append(s.get_state())
+            s.set_state(pos=state.pos, vel=state.vel)
+            s.step(5)
+            seen.append(s.get_state())
+            assert bool(h.refused) == refused
+            out.append(seen)
+    for k, (a, b) in enumerate(zip(*out)):
+        for key in a:
+            np.testing.assert_array_equal(a[key], b[key], err_msg=f"{k}: {key}")
+
+
+@pytest.mark.parametrize("n,kept", [(20000, True), (3_800_000, False)])
+def test_large_transfer_buffers_are_given_back(n, kept):
+    """The transfer buffer (72 bytes per particle) stays up to 256 MiB; a larger one does not."""
+    from paper_1506_05094_amd import srmd
+    print(f"transfer buffer of {n}", flush=True)
+    L = float(np.float32((n / gen.LJ_RHO) ** (1.0 / 3.0)))
+    pos = np.random.default_rng(n).uniform(-0.499 * L, 0.499 * L, (n, 3)).astype(np.float32)
+    with hooked() as h, srmd.System(pos, np.zeros(n, np.int32), [L] * 3, vel=pos) as s:
+        before = h.held()
+        np.testing.assert_array_equal(s.get_state()["pos"], pos)
+        assert (h.held() > before) == kept
+        s.set_state(pos=pos[::-1].copy())
+        assert (h.held() > before) == kept
+        got = s.get_state()
+        np.testing.assert_array_equal(got["pos"], pos[::-1])
+        np.testing.assert_array_equal(got["vel"], pos)
