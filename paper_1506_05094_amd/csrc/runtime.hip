@@ -80,7 +80,6 @@ constexpr int kBuildPerWave = 8;          // most particles a wave of the step k
 constexpr int kBuildPerWaveAllPairs = 2;  // the same with all-pairs lists (N candidates each: measured slower at 4 and 8)
 constexpr double kTunerListKeep = 1.05;   // list methods within 5 % of the fastest at the default layout go on to phase II
 constexpr int kPersistChunk = 500;  // steps per launch of the persistent kernel (even)
-constexpr int kAheadSlots[] = {8, 12, 20, 32};  // run-ahead chains: steps enqueued after a rebuild slot
 constexpr long long kAheadLinks = 256;  // most links enqueued before the host reads the progress
 constexpr int kAheadMin = 4;        // fewest remaining steps that run ahead
 
@@ -153,7 +152,7 @@ struct srmd_system {
   size_t h_xfer = 0;        // bytes of a state transfer that fit behind it (0: larger systems)
   char *d_xfer = nullptr;   // device copy of a state in original order (xfer_bytes)
   std::map<std::pair<int, int>, hipGraphExec_t> graphs;
-  int ahead_slots = kAheadSlots[0];  // run-ahead chains: steps after a rebuild slot
+  int ahead_slots = kAheadFirst;     // run-ahead chains: steps after a rebuild slot
   long long ahead_step = -1, ahead_builds = 0;  // steps and list builds at the last reading (-1: none yet)
   double ahead_rate = 0;             // steps done per rebuild slot, as last measured (0: not yet)
   std::string err;
@@ -883,9 +882,8 @@ srmd_status run_persistent(srmd_system *s, long long nsteps) {
 // the next slot, and all exit once the call's last step is done.  Links are enqueued for
 // the steps left at the rate that the list lasts, the host then reads how far the device
 // came and enqueues what is missing.  The slots after a rebuild follow the mean list
-// lifetime I (8 up to I = 8.5, then 12, 20, 32): fewer leave rebuild slots idle, more
-// leave steps idle.  *left: the steps not done; on return fewer than kAheadMin, or the
-// list overflowed (h->ctl is the control block as read last).
+// lifetime (ahead_slots_for).  *left: the steps not done; on return fewer than kAheadMin, or
+// the list overflowed (h->ctl is the control block as read last).
 srmd_status run_ahead(srmd_system *s, long long *left) {
   while (*left >= kAheadMin) {
     const int slots = s->ahead_slots;
@@ -902,14 +900,17 @@ srmd_status run_ahead(srmd_system *s, long long *left) {
     if (rest < 0 || done <= 0) return fail(s, SRMD_EHIP, "run-ahead chain made no progress");
     s->cur ^= (int)(done & 1);
     *left = rest;
-    // mean list lifetime since the last reading (other calls may lie between)
+    // mean list lifetime since the last reading (other calls may lie between); before it is
+    // known, links of kAheadFirst slots that did fewer than 4 steps each tell it as well (a
+    // longer life leaves a link at least half of its slots)
     const long long steps = h.step - s->ahead_step, builds = h.n_rebuilds - s->ahead_builds;
     const bool known = s->ahead_step >= 0 && steps >= 16 && builds >= 0;
     s->ahead_step = h.step;
     s->ahead_builds = h.n_rebuilds;
-    if (known) {
-      const double life = (double)steps / (double)std::max(1LL, builds);
-      s->ahead_slots = life <= 8.5 ? kAheadSlots[0] : life <= 12.5 ? kAheadSlots[1] : life <= 20.5 ? kAheadSlots[2] : kAheadSlots[3];
+    const bool told = s->ahead_rate == 0 && links >= 4 && done < 4 * links && rest > 0;
+    if (known || told) {
+      const double life = known ? (double)steps / (double)std::max(1LL, builds) : (double)done / (double)links;
+      s->ahead_slots = ahead_slots_for(life);
       s->ahead_rate = life / std::ceil(life / s->ahead_slots);
       st = get_graph(s, -s->ahead_slots, 0, &ge);  // captured now rather than in the next round
       if (st != SRMD_OK) return st;

@@ -18,6 +18,7 @@ void stage(int n, const double *L, const int *nc, const int *q, double reach, in
   out[0] = p.cap;
   out[1] = p.lds;
 }
+int slots(double life) { return srmd::ahead_slots_for(life); }
 long long list_bytes(int cap) { return (long long)srmd::stage_list_bytes(cap); }
 }
 """
@@ -36,6 +37,7 @@ def plans(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, "-o", lib, src], check=True)
     lib = ctypes.CDLL(lib)
     lib.stage.argtypes = [ctypes.c_int] + [ctypes.c_void_p] * 3 + [ctypes.c_double] + [ctypes.c_int] * 2 + [ctypes.c_void_p]
+    lib.slots.argtypes = [ctypes.c_double]
     lib.list_bytes.restype = ctypes.c_longlong
     return lib
 
@@ -85,3 +87,25 @@ def test_other_layouts_and_small_grids_take_plain_lists(plans):
     assert _stage(plans, 64000, 0.8442, 2.8, 1, 128)[0] == 0
     assert _stage(plans, 1500, 0.8442, 2.8, 1, 256)[0] == 0
     assert math.prod(_stage(plans, 1 << 28, 0.8442, 2.8, 1, 256)) == 0
+
+
+IDLE_REBUILD, IDLE_STEP = 7.5, 1.5  # us of a rebuild slot that is not due, of a step that waits for one
+
+
+def _idle(life, slots):
+    """Idle time per rebuild at a whole number of steps per list."""
+    links = -(-life // slots)
+    return (links - 1) * IDLE_REBUILD + (links * slots - life) * IDLE_STEP
+
+
+def test_run_ahead_slots_cost_no_more_than_a_slot_per_step(plans):
+    """For any list life, also one that varies by a step, run-ahead chains idle no longer than
+    a rebuild slot before every step does, and not much longer than the best of the counts."""
+    for whole in range(1, 60):
+        for part in (0.0, 0.25, 0.5, 0.75):
+            k = plans.slots(whole + part)
+            idle = lambda s: (1 - part) * _idle(whole, s) + part * _idle(whole + 1, s)
+            assert idle(k) <= (1 - part) * (whole - 1) * IDLE_REBUILD + part * whole * IDLE_REBUILD + 1e-9, (whole, part, k)
+            if whole < 3:
+                assert idle(k) <= 1.25 * min(idle(s) for s in (1, 2, 8)) + 1.0, (whole, part, k)
+
