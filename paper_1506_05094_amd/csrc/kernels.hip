@@ -730,8 +730,8 @@ __device__ __forceinline__ float wave_min_f32(float v) {
 // The copies of a workgroup's units' regions into LDS (unit after unit, place 0 of each
 // a far-away particle that no distance test passes).  Returns the first place of the
 // calling wave's unit, or -1 when its lists are plain ones (a region that was too large
-// for the list build, or for what the units before it leave of the LDS).  Every thread
-// of the block must call it; a barrier must follow.
+// for the list build); the others all fit, as stage_lds holds stage_cap places and one
+// more for every unit.  Every thread of the block must call it; a barrier must follow.
 template <int TP>
 __device__ __forceinline__ int stage_fill(const SysConst &c, const SysPtrs &p, const float4 *__restrict__ pos, int lb,
                                           float4 *s_region) {
@@ -742,7 +742,7 @@ __device__ __forceinline__ int stage_fill(const SysConst &c, const SysPtrs &p, c
   for (int u = 0; u < units; ++u) {
     if ((u0 + u) * kStageSlots >= c.n) break;
     const int n = p.stage_n[u0 + u];
-    if (n == 0 || at + n + 1 > c.stage_lds) continue;
+    if (n == 0) continue;
     if (u == mine) place = at;
     const unsigned *src = p.stage_src + (size_t)(u0 + u) * c.stage_cap;
     float4 *dst = s_region + at + 1;
