@@ -60,7 +60,7 @@ def _only_these(state, what):
     (lambda: _lj(864), None, (0, 0), 0), (lambda: _lj(864), (4, 64), (0, 1), 0), (lambda: _lj(864), (16, 16), (0, 1), -1),
     (lambda: _ka(1500), (1, 64), (0, 3), 0), (lambda: _lj(9001), (8, 32), (2, 3), 0), (lambda: _lj(9001), (2, 128), (2, 1), 20),
     (lambda: _lj(12007), (1, 256), (2, 2), 0), (lambda: _ka(12007), (4, 256), (2, 2), 0),
-    (lambda: _salt(9000), (1, 256), (2, 2), 0), (lambda: _salt(9000), (8, 32), (2, 3), 0),
+    (lambda: _salt(20011), (1, 256), (2, 2), 0), (lambda: _salt(9000), (8, 32), (2, 3), 0),
 ], ids=["default", "wave", "persistent", "cells", "large", "large-persistent", "staged", "staged-mixture", "staged-salt", "salt"])
 def test_overlapping_pair(case, launch, paths, persistent):
     from paper_1506_05094_amd import srmd
