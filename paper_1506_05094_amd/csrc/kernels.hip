@@ -665,7 +665,7 @@ __device__ __forceinline__ int wave_max_i32(int v) {
 // share a round trip.  A wave whose particles are all farther than the cutoff from
 // every face takes the loop without image arithmetic, and a system of one type the
 // loop with scalar constants (25 and 20 instructions of about 60 per pair).  SLIM: the
-// general loop only (the rare unstaged units of the staged kernels).
+// general loop only (the rare unstaged units of the staged kernels, the persistent kernel).
 template <int TP, int METHOD, int B, bool SLIM, class IdxPtr>
 __device__ __forceinline__ void force_lane(int i, int t, bool active, const float4 pi, const float4 *__restrict__ pos,
                                            IdxPtr nbl, IdxPtr nnb, const SharedPairs &sp, const SysConst &c,
@@ -2147,7 +2147,8 @@ constexpr int kCellWindow = 64 * kCellChunks;
 // the particle-by-particle builders entry for entry.  cand: kCellWindow entries of
 // the wave's LDS; cnt[l]: entries found so far for particle i0 + l (LDS, the caller
 // clears it); sink(i, k, upto, j) stores entry k of particle i (called by the hit lanes;
-// upto: entries found so far with those of this chunk, uniform).
+// upto: entries found so far with those of this chunk, uniform).  GEO: the image from the
+// cells where they tell it (else always per pair).
 
 // Lanes before this one whose bit of mask is set, plus base.
 __device__ __forceinline__ int rank_below(unsigned long long mask, int base) {
@@ -2201,7 +2202,7 @@ __device__ __forceinline__ void cell_tests(const SysConst &c, int i0, int i1, un
   }
 }
 
-template <class Cand, class Sink>
+template <bool GEO, class Cand, class Sink>
 __device__ __forceinline__ void list_cell_particles(const SysConst &c, const SysPtrs &p, int cx, int cy, int cz, int i0, int i1,
                                     Cand *cand, int *cnt, const float *s_cs2, const float4 *tpos,
                                     const unsigned *cstart, Sink sink) {
@@ -2246,7 +2247,7 @@ __device__ __forceinline__ void list_cell_particles(const SysConst &c, const Sys
         if (qi >= wlen) q[cb].x = __builtin_inff();
       }
     }
-    if (geo)
+    if (GEO && geo)
       cell_tests<false>(c, i0, i1, wlen, u, q, h, cnt, s_cs2, tpos, sink);
     else
       cell_tests<true>(c, i0, i1, wlen, u, q, h, cnt, s_cs2, tpos, sink);
@@ -2323,7 +2324,7 @@ static __global__ __launch_bounds__(64 * kCellWaves, 4) void k_list_cell(SysCons
     const int l0 = s_seg[sg], l1 = s_seg[sg + 1];
     int cx, cy, cz;
     cell_coords(p.t_pos[T0 + l0], c, cx, cy, cz);
-    list_cell_particles(c, p, cx, cy, cz, T0 + l0, T0 + l1, s_cand[wv], s_cnt + l0, s_cs2, p.t_pos, p.cell_start,
+    list_cell_particles<true>(c, p, cx, cy, cz, T0 + l0, T0 + l1, s_cand[wv], s_cnt + l0, s_cs2, p.t_pos, p.cell_start,
                         stage);
   }
   __syncthreads();
@@ -3255,7 +3256,7 @@ __device__ __forceinline__ void list_rounds(const SysConst &cg, const SysPtrs &p
       const int l0 = s_seg[par][h][q], l1 = s_seg[par][h][q + 1];
       int cx, cy, cz;
       cell_coords(tpos[T0 + l0], c, cx, cy, cz);
-      list_cell_particles(c, p, cx, cy, cz, T0 + l0, T0 + l1, cand, s_cnt[par] + l0, s_cs2, tpos, cstart, sink);
+      list_cell_particles<true>(c, p, cx, cy, cz, T0 + l0, T0 + l1, cand, s_cnt[par] + l0, s_cs2, tpos, cstart, sink);
       if (lane < l1 - l0) atomicMax(&s_kmax[par], s_cnt[par][l0 + lane]);
       if (lane == 0) sg = atomicAdd(&s_next[par], 1);
       sg = __builtin_amdgcn_readfirstlane(sg);
@@ -3320,6 +3321,18 @@ struct kMultiWaves {
 template <int TP, int NT>
 struct kMultiBatch {
   static constexpr int value = NT == kBatchThreads ? 4 : Batch<TP>::value;
+};
+
+// The persistent kernel of one small system runs its phases once per step, a few waves per
+// SIMD: its size counts, also of code that a step does not reach.  From 8 threads per
+// particle it takes the general pair loop alone, and its cell lists the image per pair alone
+// (500 steps of the liquid at 2048, 4096 and 8000 particles: 14.6, 15.5 and 19.6 us a step;
+// with the loops and tests for every case 15.3, 16.6 and 20.6; the mixture 14.2, 16.0 and
+// 19.7 against 15.2, 17.2 and 21.0).  Fewer threads per particle have more pairs per lane and
+// the large-system form more of them per wave, for which the loops without images pay.
+template <int TP, bool BIG, int NT>
+struct kMultiSlim {
+  static constexpr bool value = NT == kPersistThreads && TP >= 8 && !BIG;
 };
 
 template <int TP, int METHOD, bool BIG, int NT>
@@ -3459,7 +3472,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kMultiWaves<
           for (int l = lane; l < ne; l += 64) wcnt[l] = 0;
           int cx, cy, cz;
           cell_coords(tpos[e0], c, cx, cy, cz);
-          list_cell_particles(c, p, cx, cy, cz, (int)e0, (int)e1, cand, wcnt, s_cs2, tpos, cstart, direct);
+          list_cell_particles<BIG>(c, p, cx, cy, cz, (int)e0, (int)e1, cand, wcnt, s_cs2, tpos, cstart, direct);
           for (int l = lane; l < ne; l += 64) {
             const int cn = wcnt[l];
             p.nnb[e0 + l] = min(cn, c.n_max);
@@ -3506,7 +3519,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(kMultiWaves<
             l0 = gload(p.last, i);
           }
         }
-        force_lane<TP, METHOD, kMultiBatch<TP, NT>::value, false>(ic, t, active, pi, spos, nblg, nnbg, sp, c, fx, fy, fz,
+        force_lane<TP, METHOD, kMultiBatch<TP, NT>::value, kMultiSlim<TP, BIG, NT>::value>(ic, t, active, pi, spos, nblg, nnbg, sp, c, fx, fy, fz,
                                                                   uu, w);
         fx = lane_sum<TP>(fx);
         fy = lane_sum<TP>(fy);
