@@ -2027,8 +2027,7 @@ srmd_status srmd_save_state(srmd_system *s, void *buf, size_t bytes, size_t *nee
   HIPCHK(s, hipMemcpyAsync(&h.thermo, s->p.thermo, sizeof(Thermo), hipMemcpyDeviceToHost, s->stream));
   HIPCHK(s, hipStreamSynchronize(s->stream));
   h.ctl.list_entries = h.ctl.entries;
-  h.ctl.entries = 0;  // words that a call sets for itself are zero in the file
-  h.ctl.stop = 0;
+  h.ctl.stop = 0;  // words that a call sets for itself are zero in the file
   h.ctl.cur = 0;
   // the list is stored when it is the one the next force evaluation uses
   const long long rows = h.ctl.rebuild ? 0 : (h.ctl.max_nbrs + s->c.tp - 1) / s->c.tp;
