@@ -14,7 +14,7 @@
 //                    offsets, one workgroup per tile), k_scatter, k_gather
 //                    (deterministic rank by particle id, gather of every
 //                    per-particle array: the reorder of section 7), then the list
-//                    kernel.  A chain holds these once per 8 to 32 steps; a step
+//                    kernel.  A chain holds these once per 1 to 32 steps; a step
 //                    that finds a rebuild due exits, and so do those after it, up
 //                    to the next of these places;
 //     list kernels: k_list_wave (a wave per particle), k_list_cell (a wave per piece
