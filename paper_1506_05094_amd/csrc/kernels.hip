@@ -455,15 +455,16 @@ __device__ __forceinline__ void lj_pair(const float4 pi, const Wide &wi, const f
 // The selects of lj_pair leave a pair out of range a product with 0, which a non-finite
 // coordinate (of the neighbour, or the particle's own in an idle slot) turns into NaN; such
 // a pair contributes nothing (no distance to it is below a cutoff).  So a lane whose sums are
-// not finite takes its mine entries again one by one and leaves those out: the same sums
-// unless a pair in range is itself not finite.  entry(m): the lane's entry m.
-template <int METHOD, class Entry>
-__device__ __forceinline__ void finite_sums(const float4 pi, int mine, Entry entry, const SharedPairs &sp,
+// not finite takes its entries again one by one and leaves those out: the same sums unless a
+// pair in range is itself not finite.  count(): the lane's entries; entry(m): its entry m.
+template <int METHOD, class Count, class Entry>
+__device__ __forceinline__ void finite_sums(const float4 pi, Count count, Entry entry, const SharedPairs &sp,
                                             const SysConst &c, float &fx, float &fy, float &fz, float &u, float &w) {
   if (fabsf((fx + fy) + (fz + w)) < __builtin_inff()) return;
   const int row0 = ptype(pi) * c.ntypes;
   const Wide wi = widen(pi);
   fx = fy = fz = u = w = 0.f;
+  const int mine = count();
 #pragma unroll 1
   for (int m = 0; m < mine; ++m) {
     const float4 q = entry(m);
@@ -709,7 +710,8 @@ __device__ __forceinline__ void force_lane(int i, int t, bool active, const floa
   }
   if constexpr (METHOD <= 3)
     finite_sums<METHOD>(
-        pi, mine, [&](int m) { return pos[*(row + (long long)m * stride + lane)]; }, sp, c, fx, fy, fz, u, w);
+        pi, [&] { return mine; }, [&](int m) { return pos[*(row + (long long)m * stride + lane)]; }, sp, c, fx, fy, fz,
+        u, w);
 }
 
 // Least of the lanes' values (at most 1e30), uniform.
@@ -843,14 +845,25 @@ __device__ __forceinline__ void force_lane_staged(int i, int t, bool active, con
   } else {
     stage_loop<TP, METHOD, true, false>(pi, region, row, stride, col, mine, words, j, sp, c, fx, fy, fz, u, w);
   }
-  if constexpr (METHOD <= 3)
+  if constexpr (METHOD <= 3) {
+    // the list's length and column anew: kept over the loop above they would be spilled (two
+    // registers of each thread, 8 MB a step at 1 024 000 particles)
+    auto anew = [](int v) {
+      __asm__("" : "+v"(v));
+      return v;
+    };
     finite_sums<METHOD>(
-        pi, mine,
+        pi,
+        [&] {
+          const int nk = active ? p.nnb[anew(i)] : 0;
+          return nk > t ? (nk - t + TP - 1) / TP : 0;
+        },
         [&](int m) {
-          const unsigned two = row[(long long)(m >> 1) * stride + col];
+          const unsigned two = row[(long long)(m >> 1) * stride + (active ? anew((int)threadIdx.x) & 63 : 0)];
           return region[m & 1 ? two >> 16 : two & 0xffffu];
         },
         sp, c, fx, fy, fz, u, w);
+  }
 }
 
 // Inclusive prefix sum over the lanes of a wave, exact for integers: within each row
