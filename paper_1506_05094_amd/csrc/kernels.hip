@@ -2858,14 +2858,16 @@ __device__ void step_tail(const SysConst &c, const SysPtrs &p, int G, int next, 
 
 // Waves per SIMD the step kernel is compiled for: blocks of 1024 threads need four.  The
 // staged form at one lane per particle takes five (with float32 positions): its LDS copy
-// leaves room for five blocks of 256.
-template <int TP, int PREC, bool STAGE>
+// leaves room for five blocks of 256; but not with the further potentials (method 5), whose
+// loop then spills 40 registers (100 steps at 256 000 particles with 5 and 4 waves: Yukawa
+// 14.77 and 14.35 ms, Gaussian 9.13 and 8.95, Dzugutov 8.17 and 8.03).
+template <int TP, int METHOD, int PREC, bool STAGE>
 struct kStepWaves {
-  static constexpr int value = STAGE && TP == 1 && PREC == 0 ? 5 : 4;
+  static constexpr int value = STAGE && TP == 1 && METHOD < 5 && PREC == 0 ? 5 : 4;
 };
 
 template <int TP, int METHOD, int PREC, bool STAGE>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kStepWaves<TP, PREC, STAGE>::value))) void k_step(SysConst c, SysPtrs p, int cur, int tail) {
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kStepWaves<TP, METHOD, PREC, STAGE>::value))) void k_step(SysConst c, SysPtrs p, int cur, int tail) {
   extern __shared__ unsigned s_tail_lds[];  // list build and tail of small systems; STAGE: the region copies
   __shared__ SharedPairs sp;
   __shared__ BlockPartial s_waves[16];
