@@ -812,9 +812,13 @@ ReplicaDesc make_desc(const srmd_system *s) {
 }
 
 // The lists of staged units as plain entries in nbl, for the readers of nbl; drop: from
-// now on the units' lists are the plain ones.
+// now on the units' lists are the plain ones.  A layout whose arrays could not be made has none
+// (the constants are those of the layout, the arrays may be missing or of an earlier one).
 srmd_status plain_lists(srmd_system *s, bool drop) {
-  if (s->c.stage) HIPCHK(s, launch_stage_expand(s->stream, s->c, s->p, drop));
+  const bool made = s->p.nbl && s->p.list16 && s->p.stage_src && s->p.stage_n &&
+                    (size_t)stage_units(s->n) * (size_t)s->c.stage_cap <= s->stage_alloc &&
+                    (long long)s->c.n_max * s->c.nvp <= std::min(s->nbl_alloc, 2 * s->list16_alloc);
+  if (s->c.stage && made) HIPCHK(s, launch_stage_expand(s->stream, s->c, s->p, drop));
   return SRMD_OK;
 }
 

@@ -187,3 +187,35 @@ def test_large_transfer_buffers_are_given_back(n, kept):
         got = s.get_state()
         np.testing.assert_array_equal(got["pos"], pos[::-1])
         np.testing.assert_array_equal(got["vel"], pos)
+
+
+def test_readers_after_a_refused_layout():
+    """A change to staged lists whose cell arrays are refused leaves constants without arrays:
+    the readers of lists touch none of them, and the next call makes the layout."""
+    from paper_1506_05094_amd import srmd
+    print("refused layout, then readers", flush=True)
+    with hooked() as h, _liquid(_state(), launch=(8, 32), list_mode=3) as s, \
+            _liquid(_state(), launch=(1, 256), list_mode=1) as ref:
+        s.step(5)
+        s.set_launch(1, 256)
+        s.set_rebuild_path(2, 2)
+        s.set_skin(0.1)  # more cells: their arrays are made anew
+        h.refuse = lambda sizes, nbytes: True
+        for call in (lambda: s.step(5), s.save_state, s.compute_forces):
+            with pytest.raises(srmd.SrmdError) as e:
+                call()
+            assert e.value.status == srmd.SRMD_ENOMEM
+        with contextlib.suppress(srmd.SrmdError):
+            s.neighbor_pairs()
+        h.refuse = lambda sizes, nbytes: False
+        start = s.get_state()
+        s.step(10)
+        ref.set_skin(0.1)
+        ref.set_state(pos=start["pos"], vel=start["vel"])
+        s.set_state(pos=start["pos"], vel=start["vel"])
+        s.step(10)
+        ref.step(10)
+        np.testing.assert_array_equal(s.neighbor_pairs(), ref.neighbor_pairs())
+        a, b = s.get_state(), ref.get_state()
+        for k in ("pos", "vel", "force"):
+            np.testing.assert_array_equal(a[k], b[k], err_msg=k)
