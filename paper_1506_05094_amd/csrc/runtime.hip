@@ -829,6 +829,7 @@ srmd_status launch_persistent(srmd_system *s, int cnt) {
   if (g > s->jobs_cap) {
     dev_free(s, s->d_jobs);
     dev_free(s, s->d_job_off);
+    s->jobs_cap = s->jobs_g = 0;
     s->d_jobs = (CoopJob *)need_alloc(s, sizeof(CoopJob) * (size_t)g);
     s->d_job_off = (int *)need_alloc(s, sizeof(int) * (size_t)(g + 1));
     if (!s->d_jobs || !s->d_job_off) return fail(s, SRMD_ENOMEM, "persistent job table allocation failed");

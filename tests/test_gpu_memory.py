@@ -219,3 +219,22 @@ def test_readers_after_a_refused_layout():
         a, b = s.get_state(), ref.get_state()
         for k in ("pos", "vel", "force"):
             np.testing.assert_array_equal(a[k], b[k], err_msg=k)
+
+
+def test_fewer_groups_after_a_refused_job_table():
+    """A persistent job table that could not grow leaves none behind either."""
+    from paper_1506_05094_amd import srmd
+    print("refused job table", flush=True)
+    state = _state(2000)
+    with hooked() as h, _liquid(state, launch=(8, 32)) as s, _liquid(state, launch=(8, 32)) as ref:
+        s.set_persistent(4)
+        s.step(3)
+        s.set_persistent(40)
+        h.refuse = lambda sizes, nbytes: nbytes == 40 * 16  # the table of 40 jobs
+        with pytest.raises(srmd.SrmdError) as e:
+            s.step(3)
+        assert h.refused and e.value.status == srmd.SRMD_ENOMEM
+        s.set_persistent(3)
+        s.step(3)
+        ref.step(6)
+        np.testing.assert_array_equal(s.get_state()["pos"], ref.get_state()["pos"])
